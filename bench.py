@@ -28,7 +28,7 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 METRIC = "effective GFLOP/s (5N·log2N) + HBM GB/s % peak, 512^3 c64 FP32 vs MFMA vs batched"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_512cube.json")
-KERNEL_SOURCES = ["paper_1302_6189_amd/csrc/fft_pow2.hip", "paper_1302_6189_amd/csrc/xpose_tile.hpp",
+KERNEL_SOURCES = ["paper_1302_6189_amd/csrc/fft_ct.hpp", "paper_1302_6189_amd/csrc/xpose_tile.hpp",
                   "paper_1302_6189_amd/csrc/cplx.hpp", "paper_1302_6189_amd/csrc/kernels.hpp"]
 
 
@@ -435,13 +435,13 @@ def main():
         # 2 transforms per step): its average duration is the region's time,
         # bracketed by HIP events on the exec stream, over its launches (the
         # gaps between launches, under 1%, included)
-        kernels = {"fft_xpose_kernel": {"avg_ms": ms_per_step / (2 * len(stage_ms)),
+        kernels = {"ct_fused_kernel": {"avg_ms": ms_per_step / (2 * len(stage_ms)),
                                         "launches_per_transform": len(stage_ms),
                                         "avg_ms_stage_events": sum(stage_ms) / len(stage_ms)}}
     else:
         fft_ms, xp_ms = stage_ms[0::2], stage_ms[1::2]
         kernels = {
-            "fft_pow2_kernel": {"avg_ms": sum(fft_ms) / len(fft_ms), "launches_per_transform": len(fft_ms)},
+            "ct_rows_kernel": {"avg_ms": sum(fft_ms) / len(fft_ms), "launches_per_transform": len(fft_ms)},
             "xpose_kernel": {"avg_ms": sum(xp_ms) / len(xp_ms), "launches_per_transform": len(xp_ms)},
         }
     dom = max(kernels, key=lambda n: kernels[n]["avg_ms"] * kernels[n]["launches_per_transform"])

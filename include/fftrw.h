@@ -249,11 +249,10 @@ int fft_compare_models(double N, double P, double *out);
  * fused permutation.
  * Fusion: unless flags hold FFTRW_FLAG_SEPARATE or FFTRW_FLAG_STAGED, each
  * FFT step runs fused with the transpose that follows it when every step
- * qualifies (power-of-two rows of 16..512 points for C64, 16..256 for C128,
- * whose work-group's run along the next layout's last axis fits that axis;
- * other 2,3,5-smooth rows up to 4095 points for C64, 2047 for C128; 256- and
- * 512-point rows of the split MFMA forms); otherwise, and for execs with in == out, the
- * steps and transposes run as separate kernels.  Results are bit-identical
+ * qualifies (rows of any supported length up to 4096 points for C64, 2048 for
+ * C128; 256- and 512-point rows of the split MFMA forms); otherwise the steps
+ * and transposes run as separate kernels.  Execs with in == out take one copy
+ * more when the number of transposes is odd.  Results are bit-identical
  * either way; fft_plan_describe's text starts with "fused|" when it fuses.
  * The plan owns its device workspace (fft_workspace_bytes) and twiddle
  * tables; it must outlive every exec enqueued with it.  One exec per plan may

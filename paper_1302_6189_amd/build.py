@@ -16,8 +16,9 @@ LIB = os.path.join(HERE, "libfftrw.so")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 HIPCC = os.path.join(ROCM, "bin", "hipcc")
 
-HIP_SOURCES = ["fft_rows.hip", "fft_pow2.hip", "fft_mfma.hip", "transpose.hip", "staged.hip", "exec.hip", "batch.hip",
+HIP_SOURCES = ["fft_rows.hip", "fft_ct_launch.hip", "fft_mfma.hip", "transpose.hip", "staged.hip", "exec.hip", "batch.hip",
                "autotune.hip", "noalloc.hip", "rowsplit.hip"]
+CT_SOURCE, CT_PARTS = "fft_ct.hip", 16  # the compile-time kernels, one object per share of the lengths
 CXX_SOURCES = ["decomp.cpp", "capi_host.cpp"]
 
 HIP_FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
@@ -37,6 +38,11 @@ def _run(cmd):
 def build(verbose: bool = False, jobs: int = 8) -> str:
     os.makedirs(OUT_DIR, exist_ok=True)
     cmds, objs = [], []
+    for part in range(CT_PARTS):
+        obj = os.path.join(OUT_DIR, f"{CT_SOURCE}.{part}.o")
+        cmds.append([HIPCC, *HIP_FLAGS, f"-DFFTRW_CT_PARTS={CT_PARTS}", f"-DFFTRW_CT_PART={part}", "-c",
+                     os.path.join(CSRC, CT_SOURCE), "-o", obj])
+        objs.append(obj)
     for src in HIP_SOURCES:
         obj = os.path.join(OUT_DIR, src + ".o")
         cmds.append([HIPCC, *HIP_FLAGS, "-c", os.path.join(CSRC, src), "-o", obj])

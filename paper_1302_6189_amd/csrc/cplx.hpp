@@ -4,6 +4,11 @@
 // 1-D DFT of Eq. (1), with w = exp(DIR * 2 pi i / R): DIR = -1 is the paper's
 // forward transform, DIR = +1 the (unscaled) inverse.  The formulas are the
 // usual splittings of that sum into even/odd or symmetric parts.
+//
+// Every product that is added to something is written as a fused
+// multiply-add, so no contraction is left to the compiler: the same
+// butterflies give the same bits in every kernel they are inlined in (the
+// fused and the separate kernels of a step are compared bit for bit).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -72,14 +77,21 @@ template <typename C> __device__ __forceinline__ C mk(typename RealOf<C>::type x
 }
 template <typename C> __device__ __forceinline__ C cadd(C a, C b) { return mk<C>(a.x + b.x, a.y + b.y); }
 template <typename C> __device__ __forceinline__ C csub(C a, C b) { return mk<C>(a.x - b.x, a.y - b.y); }
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 template <typename C> __device__ __forceinline__ C cmul(C a, C b)
 {
-    return mk<C>(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+    return mk<C>(fma_(a.x, b.x, -(a.y * b.y)), fma_(a.x, b.y, a.y * b.x));
 }
 // a * conj(b)
 template <typename C> __device__ __forceinline__ C cmulc(C a, C b)
 {
-    return mk<C>(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
+    return mk<C>(fma_(a.x, b.x, a.y * b.y), fma_(a.y, b.x, -(a.x * b.y)));
+}
+// c + s a
+template <typename C> __device__ __forceinline__ C cfma(typename RealOf<C>::type s, C a, C c)
+{
+    return mk<C>(fma_(s, a.x, c.x), fma_(s, a.y, c.y));
 }
 template <typename C> __device__ __forceinline__ C cscale(C a, typename RealOf<C>::type s)
 {
@@ -128,57 +140,70 @@ template <int DIR, typename C> struct Dft<8, DIR, C> {
         C o[4] = {x[1], x[3], x[5], x[7]};
         Dft<4, DIR, C>::run(e);
         Dft<4, DIR, C>::run(o);
-        // w8^k = (cos(pi k/4), DIR sin(pi k/4))
-        C o1 = mk<C>(h * (o[1].x - DIR * o[1].y), h * (o[1].y + DIR * o[1].x));
+        // w8^k = (cos(pi k/4), DIR sin(pi k/4)): odd k are h times a sum or
+        // difference of the parts, added with one fma each
+        C o1 = mk<C>(o[1].x - DIR * o[1].y, o[1].y + DIR * o[1].x);
         C o2 = rot90<DIR>(o[2]);
-        C o3 = mk<C>(h * (-o[3].x - DIR * o[3].y), h * (-o[3].y + DIR * o[3].x));
+        C o3 = mk<C>(-o[3].x - DIR * o[3].y, -o[3].y + DIR * o[3].x);
         x[0] = cadd(e[0], o[0]);
         x[4] = csub(e[0], o[0]);
-        x[1] = cadd(e[1], o1);
-        x[5] = csub(e[1], o1);
+        x[1] = cfma(h, o1, e[1]);
+        x[5] = cfma(-h, o1, e[1]);
         x[2] = cadd(e[2], o2);
         x[6] = csub(e[2], o2);
-        x[3] = cadd(e[3], o3);
-        x[7] = csub(e[3], o3);
+        x[3] = cfma(h, o3, e[3]);
+        x[7] = cfma(-h, o3, e[3]);
     }
 };
 
+// 4 x 4: column DFTs, twiddles w16^{i k}, row DFTs
 template <int DIR, typename C> struct Dft<16, DIR, C> {
     static __device__ __forceinline__ void run(C *x)
     {
         using Real = typename RealOf<C>::type;
-        // cos(pi k / 8), sin(pi k / 8), k = 0..7
-        const Real cs[8] = {(Real)1.0,
-                            (Real)0.92387953251128675612818318939679,
-                            (Real)0.70710678118654752440084436210485,
-                            (Real)0.38268343236508977172845998403040,
-                            (Real)0.0,
-                            (Real)-0.38268343236508977172845998403040,
-                            (Real)-0.70710678118654752440084436210485,
-                            (Real)-0.92387953251128675612818318939679};
-        const Real sn[8] = {(Real)0.0,
-                            (Real)0.38268343236508977172845998403040,
-                            (Real)0.70710678118654752440084436210485,
-                            (Real)0.92387953251128675612818318939679,
-                            (Real)1.0,
-                            (Real)0.92387953251128675612818318939679,
-                            (Real)0.70710678118654752440084436210485,
-                            (Real)0.38268343236508977172845998403040};
-        C e[8], o[8];
+        const Real h = (Real)0.70710678118654752440084436210485;
+        const Real c1 = (Real)0.92387953251128675612818318939679;  // cos(pi/8)
+        const Real s1 = (Real)0.38268343236508977172845998403040;  // sin(pi/8)
+        const C w1 = mk<C>(c1, DIR * s1), w3 = mk<C>(s1, DIR * c1), w9 = mk<C>(-c1, -DIR * s1);
+        C c[4][4];  // c[n][k]: column n (inputs n + 4 i), output k
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            e[j] = x[2 * j];
-            o[j] = x[2 * j + 1];
-        }
-        Dft<8, DIR, C>::run(e);
-        Dft<8, DIR, C>::run(o);
+        for (int n = 0; n < 4; ++n) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            C w = mk<C>(cs[k], DIR * sn[k]);
-            C t = cmul(o[k], w);
-            x[k] = cadd(e[k], t);
-            x[k + 8] = csub(e[k], t);
+            for (int i = 0; i < 4; ++i) c[n][i] = x[n + 4 * i];
+            Dft<4, DIR, C>::run(c[n]);
         }
+        // terms that w16^2 = h (1 + DIR i) or w16^6 = h (-1 + DIR i) multiplies
+        // keep the factor h for the fma that adds them
+        const C t12 = mk<C>(c[1][2].x - DIR * c[1][2].y, c[1][2].y + DIR * c[1][2].x);
+        const C t21 = mk<C>(c[2][1].x - DIR * c[2][1].y, c[2][1].y + DIR * c[2][1].x);
+        const C t23 = mk<C>(-c[2][3].x - DIR * c[2][3].y, -c[2][3].y + DIR * c[2][3].x);
+        const C t32 = mk<C>(-c[3][2].x - DIR * c[3][2].y, -c[3][2].y + DIR * c[3][2].x);
+        // row 0: no twiddles
+        C r0[4] = {c[0][0], c[1][0], c[2][0], c[3][0]};
+        Dft<4, DIR, C>::run(r0);
+        // rows 1 and 3: column 2 enters times h
+        auto odd = [&](C z0, C z1, C t2, C z3, int k) {
+            const C a = cfma(h, t2, z0), b = cfma(-h, t2, z0);
+            const C c_ = cadd(z1, z3), d = rot90<DIR>(csub(z1, z3));
+            x[k] = cadd(a, c_);
+            x[k + 8] = csub(a, c_);
+            x[k + 4] = cadd(b, d);
+            x[k + 12] = csub(b, d);
+        };
+        odd(c[0][1], cmul(c[1][1], w1), t21, cmul(c[3][1], w3), 1);
+        odd(c[0][3], cmul(c[1][3], w3), t23, cmul(c[3][3], w9), 3);
+        // row 2: columns 1 and 3 enter times h, column 2 times DIR i
+        {
+            const C z2 = rot90<DIR>(c[2][2]);
+            const C a = cadd(c[0][2], z2), b = csub(c[0][2], z2);
+            const C p = cadd(t12, t32), q = rot90<DIR>(csub(t12, t32));
+            x[2] = cfma(h, p, a);
+            x[10] = cfma(-h, p, a);
+            x[6] = cfma(h, q, b);
+            x[14] = cfma(-h, q, b);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[4 * i] = r0[i];
     }
 };
 
@@ -188,11 +213,11 @@ template <int DIR, typename C> struct Dft<3, DIR, C> {
         using Real = typename RealOf<C>::type;
         const Real s3 = (Real)0.86602540378443864676372317075294;
         C t = cadd(x[1], x[2]);
-        C m = mk<C>(x[0].x - (Real)0.5 * t.x, x[0].y - (Real)0.5 * t.y);
-        C s = rot90<DIR>(cscale(csub(x[1], x[2]), s3));
+        C m = cfma((Real)-0.5, t, x[0]);
+        C s = rot90<DIR>(csub(x[1], x[2]));
         x[0] = cadd(x[0], t);
-        x[1] = cadd(m, s);
-        x[2] = csub(m, s);
+        x[1] = cfma(s3, s, m);
+        x[2] = cfma(-s3, s, m);
     }
 };
 
@@ -203,19 +228,83 @@ template <int DIR, typename C> struct Dft<5, DIR, C> {
         const Real c1 = (Real)0.30901699437494742410229341718282;   // cos(2 pi/5)
         const Real c2 = (Real)-0.80901699437494742410229341718282;  // cos(4 pi/5)
         const Real s1 = (Real)0.95105651629515357211643933337938;   // sin(2 pi/5)
-        const Real s2 = (Real)0.58778525229247312916870595463907;   // sin(4 pi/5)
+        const Real q = (Real)0.61803398874989484820458683436564;    // sin(4 pi/5) / sin(2 pi/5)
         C a1 = cadd(x[1], x[4]), a2 = cadd(x[2], x[3]);
-        C b1 = csub(x[1], x[4]), b2 = csub(x[2], x[3]);
+        C b1 = rot90<DIR>(csub(x[1], x[4])), b2 = rot90<DIR>(csub(x[2], x[3]));
         C y0 = cadd(x[0], cadd(a1, a2));
-        C m1 = mk<C>(x[0].x + c1 * a1.x + c2 * a2.x, x[0].y + c1 * a1.y + c2 * a2.y);
-        C m2 = mk<C>(x[0].x + c2 * a1.x + c1 * a2.x, x[0].y + c2 * a1.y + c1 * a2.y);
-        C n1 = rot90<DIR>(mk<C>(s1 * b1.x + s2 * b2.x, s1 * b1.y + s2 * b2.y));
-        C n2 = rot90<DIR>(mk<C>(s2 * b1.x - s1 * b2.x, s2 * b1.y - s1 * b2.y));
+        C m1 = cfma(c2, a2, cfma(c1, a1, x[0]));
+        C m2 = cfma(c1, a2, cfma(c2, a1, x[0]));
+        C n1 = cfma(q, b2, b1);
+        C n2 = cfma(q, b1, mk<C>(-b2.x, -b2.y));
         x[0] = y0;
-        x[1] = cadd(m1, n1);
-        x[4] = csub(m1, n1);
-        x[2] = cadd(m2, n2);
-        x[3] = csub(m2, n2);
+        x[1] = cfma(s1, n1, m1);
+        x[4] = cfma(-s1, n1, m1);
+        x[2] = cfma(s1, n2, m2);
+        x[3] = cfma(-s1, n2, m2);
+    }
+};
+
+// Length A B with coprime A and B (Good 1958): input (B a + A b) mod A B and
+// output k with k = ka mod A, k = kb mod B turn the sum into an A x B DFT with
+// no twiddles in between.
+template <int A, int B, int DIR, typename C> struct DftCoprime {
+    static constexpr int out(int ka, int kb)
+    {
+        int k = ka;
+        while (k % B != kb) k += A;
+        return k;
+    }
+    static __device__ __forceinline__ void run(C *x)
+    {
+        C t[A][B];
+#pragma unroll
+        for (int a = 0; a < A; ++a) {
+#pragma unroll
+            for (int b = 0; b < B; ++b) t[a][b] = x[(B * a + A * b) % (A * B)];
+            Dft<B, DIR, C>::run(t[a]);
+        }
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            C r[A];
+#pragma unroll
+            for (int a = 0; a < A; ++a) r[a] = t[a][b];
+            Dft<A, DIR, C>::run(r);
+#pragma unroll
+            for (int a = 0; a < A; ++a) x[out(a, b)] = r[a];
+        }
+    }
+};
+template <int DIR, typename C> struct Dft<6, DIR, C> : DftCoprime<2, 3, DIR, C> {};
+template <int DIR, typename C> struct Dft<10, DIR, C> : DftCoprime<2, 5, DIR, C> {};
+template <int DIR, typename C> struct Dft<12, DIR, C> : DftCoprime<4, 3, DIR, C> {};
+template <int DIR, typename C> struct Dft<15, DIR, C> : DftCoprime<3, 5, DIR, C> {};
+
+// 3 x 3: column DFTs, twiddles w9^{i k}, row DFTs
+template <int DIR, typename C> struct Dft<9, DIR, C> {
+    static __device__ __forceinline__ void run(C *x)
+    {
+        using Real = typename RealOf<C>::type;
+        const C w1 = mk<C>((Real)0.76604444311897803520239265055542, DIR * (Real)0.64278760968653932632264340990726);
+        const C w2 = mk<C>((Real)0.17364817766693034885171662676931, DIR * (Real)0.98480775301220805936674302458952);
+        const C w4 = mk<C>((Real)-0.93969262078590838405410927732473, DIR * (Real)0.34202014332566873304409961468226);
+        C c[3][3];
+#pragma unroll
+        for (int n = 0; n < 3; ++n) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i) c[n][i] = x[n + 3 * i];
+            Dft<3, DIR, C>::run(c[n]);
+        }
+        c[1][1] = cmul(c[1][1], w1);
+        c[1][2] = cmul(c[1][2], w2);
+        c[2][1] = cmul(c[2][1], w2);
+        c[2][2] = cmul(c[2][2], w4);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            C r[3] = {c[0][k], c[1][k], c[2][k]};
+            Dft<3, DIR, C>::run(r);
+#pragma unroll
+            for (int i = 0; i < 3; ++i) x[k + 3 * i] = r[i];
+        }
     }
 };
 

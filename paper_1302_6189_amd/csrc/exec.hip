@@ -24,16 +24,16 @@
 namespace fftrw {
 
 hipError_t launch_twiddles(void *out, int64_t n, bool fp64, hipStream_t s);
-bool pow2_supported(int N, bool fp64);
-void pow2_describe(int N, bool fp64, int *tw_count, int *radices, int *npass);
-hipError_t pow2_make_twiddles(int N, bool fp64, void *tw, hipStream_t s);
-hipError_t launch_fft_pow2(int N, bool fp64, const void *tw, int64_t nrows, int dir, const void *in, void *out,
-                           double scale, hipStream_t s);
-int pow2_rows_per_wg(int N, bool fp64);
+bool ct_supported(int N, bool fp64);
+void ct_describe(int N, bool fp64, int *tw_count, int *radices, int *npass);
+hipError_t ct_make_twiddles(int N, bool fp64, void *tw, hipStream_t s);
+bool ct_plan_step(int N, bool fp64, const XposeDesc &d, CtStep *step);
+hipError_t launch_ct_fused(const CtStep &step, const void *tw, const XposeDesc &d, int dir, const void *in, void *out,
+                           double scale, CachePolicy policy, hipStream_t s);
+hipError_t launch_ct_rows(int N, bool fp64, const void *tw, int64_t nrows, int dir, const void *in, void *out,
+                          double scale, CachePolicy policy, hipStream_t s);
 hipError_t launch_fft_xpose_generic(const FftDesc &f, const XposeDesc &d, bool fp64, int dir, const void *in,
                                     void *out, double scale, hipStream_t s);
-hipError_t launch_fft_xpose_pow2(int N, bool fp64, const void *tw, const XposeDesc &fx, int dir, const void *in,
-                                 void *out, double scale, hipStream_t s);
 hipError_t launch_fft_mfma_xpose(int precision, int dir, int N, const void *twN, const XposeDesc &d, const void *in,
                                  void *out, double scale, hipStream_t s);
 hipError_t launch_fft_mfma(int precision, int dir, int N, const void *twN, int64_t nrows, const void *in, void *out,
@@ -136,9 +136,9 @@ int make_len_desc(fft_plan_impl *pl, i64 N, FftDesc *d, bool generic_rows, const
         d->tw_count = (int)N;
         return FFTRW_OK;
     }
-    if (!generic_rows && pow2_supported((int)N, pl->esz == 16)) {
-        d->pow2 = 1;
-        pow2_describe((int)N, pl->esz == 16, &d->tw_count, d->radix, &d->npass);
+    if (!generic_rows && ct_supported((int)N, pl->esz == 16)) {
+        d->ct = 1;
+        ct_describe((int)N, pl->esz == 16, &d->tw_count, d->radix, &d->npass);
         return FFTRW_OK;
     }
     d->npass = factor_radices(N, d->radix);
@@ -187,7 +187,7 @@ int make_desc_twiddles(fft_plan_impl *pl, const FftDesc &d, void **tw)
 {
     if (int rc = dev_alloc(pl, tw, (size_t)std::max(1, d.tw_count) * pl->esz)) return rc;
     hipStream_t ts = pl->arena ? pl->arena->stream : nullptr;
-    hipError_t e = (d.pow2 && !d.mfma) ? pow2_make_twiddles(d.N, pl->esz == 16, *tw, ts)
+    hipError_t e = (d.ct && !d.mfma) ? ct_make_twiddles(d.N, pl->esz == 16, *tw, ts)
                                        : launch_twiddles(*tw, d.N, pl->esz == 16, ts);
     if (e != hipSuccess) return hip_fail(e, "twiddle generation");
     return FFTRW_OK;
@@ -305,6 +305,28 @@ int dev_alloc(fft_plan_impl *pl, void **p, size_t bytes)
     return FFTRW_OK;
 }
 
+// Whether a pass over the array streams or caches.  The 256 MB Infinity Cache
+// keeps what cached stores leave for the next pass (a plain copy of up to
+// 128 MB runs at 8.4 TB/s cached and 6.5 streaming), if loads that nothing
+// repeats do not push it out: loads stream once the pass's two arrays come
+// near its size.  Forward transforms with cached / streaming loads:
+// 160^3 (33 MB) 40 / 44 us, 192^3 (57 MB) 63 / 64, 240^3 121 / 112, 288^3
+// 240 / 199, 512^3 1167 / 1137.
+// Stores are cached except
+//   * from 1 GB on, where little of them survives (streaming / cached:
+//     480^3 1047 / 1038, 512^3 1137 / 1162);
+//   * while the L2s hold the array, as dirty lines are written back when a
+//     kernel ends (96^3 17.9 / 19.8, 128^3 25.4 / 27.5; 144^3 42.7 / 37.8);
+//   * in the last step, whose output no later step reads (256^3 131.9 / 139.8);
+// and always where a run ends inside a line, whose parts only the caches can
+// join (4096x2048: streaming 144, cached 72).
+CachePolicy cache_policy(const fft_plan_impl *pl, bool last, bool whole_lines)
+{
+    const size_t bytes = (size_t)pl->T * pl->esz;
+    return {bytes > ((size_t)64 << 20),
+            whole_lines && (bytes >= (size_t)1000000000 || bytes <= ((size_t)20 << 20) || last)};
+}
+
 int run_fft_desc(fft_plan_impl *pl, const FftDesc &d, int dir, const void *in, void *out, double scale,
                  hipStream_t s)
 {
@@ -312,8 +334,9 @@ int run_fft_desc(fft_plan_impl *pl, const FftDesc &d, int dir, const void *in, v
         HIP_TRY(launch_fft_mfma(d.mfma, dir, d.N, d.tw, d.nrows, in, out, scale, s), "mfma fft pass launch");
         return FFTRW_OK;
     }
-    if (d.pow2) {
-        HIP_TRY(launch_fft_pow2(d.N, pl->esz == 16, d.tw, d.nrows, dir, in, out, scale, s), "fft pass launch");
+    if (d.ct) {
+        HIP_TRY(launch_ct_rows(d.N, pl->esz == 16, d.tw, d.nrows, dir, in, out, scale, cache_policy(pl, false, true), s),
+                "fft pass launch");
         return FFTRW_OK;
     }
     HIP_TRY(launch_fft_rows(d, pl->esz == 16, dir, in, out, scale, s), "fft pass launch");
@@ -357,6 +380,29 @@ int run_transpose(fft_plan_impl *pl, int t, const void *in, void *out, hipStream
     return FFTRW_OK;
 }
 
+// destination of fused step t of nx
+void *fused_dst(fft_plan_impl *pl, int nx, int t, bool flip, void *out)
+{
+    return ((nx - 1 - t) % 2 == 0) != flip ? out : pl->work;
+}
+
+int run_fused_step(fft_plan_impl *pl, int t, int nx, int dir, const void *src, void *dst, hipStream_t s)
+{
+    const double scale = (dir > 0 && t == pl->M - 1) ? 1.0 / (double)pl->T : 1.0;
+    const FftDesc &d = pl->fft[t];
+    if (pl->fuse_kind[t] == 1)
+        HIP_TRY(launch_ct_fused(pl->ct_step[t], d.tw, pl->xp[t], dir, src, dst, scale,
+                                cache_policy(pl, t == nx - 1, pl->ct_step[t].whole), s),
+                "fused fft+transpose launch");
+    else if (pl->fuse_kind[t] == 3)
+        HIP_TRY(launch_fft_mfma_xpose(d.mfma, dir, d.N, d.tw, pl->xp[t], src, dst, scale, s),
+                "fused mfma fft+transpose launch");
+    else
+        HIP_TRY(launch_fft_xpose_generic(d, pl->xp[t], pl->esz == 16, dir, src, dst, scale, s),
+                "fused fft+transpose launch");
+    return FFTRW_OK;
+}
+
 int run_pipeline(fft_plan_impl *pl, const void *in, void *out, hipStream_t s, int dir)
 {
     const int M = pl->M;
@@ -370,30 +416,25 @@ int run_pipeline(fft_plan_impl *pl, const void *in, void *out, hipStream_t s, in
         return FFTRW_OK;
     };
     if (int rc = mark()) return rc;
-    if (pl->fused && in != out) {
+    if (pl->fused) {
         // every step is one out-of-place kernel: FFT along u, written in the
-        // next layout; the buffers alternate so the last one lands in out
+        // next layout; the buffers alternate so the last one lands in out.
+        // In place that takes an even number of steps (or a last step of rows
+        // alone); otherwise the steps end in the workspace and are copied.
+        const bool flip = in == out && nx % 2 != 0;
         const void *src = in;
         for (int t = 0; t < nx; ++t) {
-            void *dst = ((nx - 1 - t) % 2 == 0) ? out : pl->work;
-            const double scale = (dir > 0 && t == M - 1) ? 1.0 / (double)pl->T : 1.0;
-            const FftDesc &d = pl->fft[t];
-            if (pl->fuse_kind[t] == 1)
-                HIP_TRY(launch_fft_xpose_pow2(d.N, pl->esz == 16, d.tw, pl->xp[t], dir, src, dst, scale, s),
-                        "fused fft+transpose launch");
-            else if (pl->fuse_kind[t] == 3)
-                HIP_TRY(launch_fft_mfma_xpose(d.mfma, dir, d.N, d.tw, pl->xp[t], src, dst, scale, s),
-                        "fused mfma fft+transpose launch");
-            else
-                HIP_TRY(launch_fft_xpose_generic(d, pl->xp[t], pl->esz == 16, dir, src, dst, scale, s),
-                        "fused fft+transpose launch");
+            void *dst = fused_dst(pl, nx, t, flip, out);
+            if (int rc = run_fused_step(pl, t, nx, dir, src, dst, s)) return rc;
             if (int rc = mark()) return rc;
             src = dst;
         }
         if (leave) {
             const double scale = dir > 0 ? 1.0 / (double)pl->T : 1.0;
-            if (int rc = run_fft_step(pl, M - 1, dir, out, out, scale, s)) return rc;
+            if (int rc = run_fft_step(pl, M - 1, dir, src, out, scale, s)) return rc;
             if (int rc = mark()) return rc;
+        } else if (flip) {
+            HIP_TRY(hipMemcpyAsync(out, src, (size_t)pl->T * pl->esz, hipMemcpyDeviceToDevice, s), "copy to the output");
         }
         pl->n_recorded = nev;
         pl->executed = true;
@@ -525,7 +566,7 @@ int plan_create(fft_plan_t *plan, int M, const int64_t *dims, int64_t P, const i
                 return rc;
             }
             hipStream_t ts = arena ? arena->stream : nullptr;
-            hipError_t e = (pl->fft[t].pow2 && !pl->fft[t].mfma) ? pow2_make_twiddles(N, pl->esz == 16, tw, ts)
+            hipError_t e = (pl->fft[t].ct && !pl->fft[t].mfma) ? ct_make_twiddles(N, pl->esz == 16, tw, ts)
                                                                  : launch_twiddles(tw, N, pl->esz == 16, ts);
             if (e != hipSuccess) {
                 free_plan(pl);
@@ -655,10 +696,9 @@ int plan_create(fft_plan_t *plan, int M, const int64_t *dims, int64_t P, const i
         bool ok = true;
         for (int t = 0; t < nx && ok; ++t) {
             const FftDesc &d = pl->fft[t];
-            const bool pow2_ok = d.pow2 && !d.mfma && d.N >= 16 && d.N <= (fp64 ? 256 : 512) &&
-                                 pow2_rows_per_wg(d.N, fp64) <= pl->xp[t].Nv;
-            const bool generic_ok = !d.pow2 && !d.mfma && d.N + 1 <= (fp64 ? 2048 : 4096);
-            pl->fuse_kind[t] = d.mfma ? 3 : (pow2_ok ? 1 : (generic_ok ? 2 : 0));
+            const bool ct_ok = d.ct && !d.mfma && ct_plan_step(d.N, fp64, pl->xp[t], &pl->ct_step[t]);
+            const bool generic_ok = !d.ct && !d.mfma && d.N + 1 <= (fp64 ? 2048 : 4096);
+            pl->fuse_kind[t] = d.mfma ? 3 : (ct_ok ? 1 : (generic_ok ? 2 : 0));
             ok = pl->fuse_kind[t] != 0;
         }
         pl->fused = ok;

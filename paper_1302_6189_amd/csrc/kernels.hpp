@@ -16,6 +16,11 @@ constexpr int kCountSlots = 32;
 constexpr int kCountStride = 16;  // 64-bit words between slots
 constexpr int kCountBlock = kCountSlots * kCountStride;
 
+// Streaming (non-temporal) or cached HBM accesses of a pass over the array.
+struct CachePolicy {
+    bool nt_load, nt_store;
+};
+
 // One batched 1-D FFT pass set: nrows contiguous rows of length N, transformed
 // by Stockham autosort passes with the given radices (product = N).
 struct FftDesc {
@@ -26,8 +31,8 @@ struct FftDesc {
     int lanes_per_row; // 256 / RW threads cooperate on one row
     int64_t nrows;
     const void *tw;    // forward twiddles w_N^e, e = 0..N-1 (float2 or double2),
-                       // or the per-pass table of the power-of-two kernel
-    int pow2;          // 1: compile-time power-of-two kernel (fft_pow2.hip)
+                       // or the per-pass table of the compile-time kernels
+    int ct;            // 1: compile-time kernel of its length (fft_ct.hpp)
     int mfma;          // > 0: 256/512-point split-precision MFMA kernel (fft_mfma.hip)
     int tw_count;      // entries in the twiddle table
 };
