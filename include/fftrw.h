@@ -250,8 +250,8 @@ int fft_compare_models(double N, double P, double *out);
  * Fusion: unless flags hold FFTRW_FLAG_SEPARATE or FFTRW_FLAG_STAGED, each
  * FFT step runs fused with the transpose that follows it when every step
  * qualifies (rows of any supported length up to 4096 points for C64, 2048 for
- * C128; 256- and 512-point rows of the split MFMA forms); otherwise the steps
- * and transposes run as separate kernels.  Execs with in == out take one copy
+ * C128; in a plan of a split MFMA form, rows of up to 512 points); otherwise
+ * the steps and transposes run as separate kernels.  Execs with in == out take one copy
  * more when the number of transposes is odd.  Results are bit-identical
  * either way; fft_plan_describe's text starts with "fused|" when it fuses.
  * The plan owns its device workspace (fft_workspace_bytes) and twiddle

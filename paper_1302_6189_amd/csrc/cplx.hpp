@@ -13,6 +13,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 namespace fftrw {
 
 template <typename Real> struct CplxOf;
@@ -47,6 +49,23 @@ template <typename T> __device__ __forceinline__ T gld_nt(const T *p)
 template <typename T> __device__ __forceinline__ void gst_nt(T v, T *p)
 {
     __builtin_nontemporal_store(v, (__attribute__((address_space(1))) T *)p);
+}
+template <typename T> __device__ __forceinline__ void gst(T v, T *p) { *(__attribute__((address_space(1))) T *)p = v; }
+// Calls f(std::true_type()) or f(std::false_type()) by a uniform choice of
+// streaming or cached accesses.  Of two branches that differ in the kind of
+// their accesses alone the compiler makes one, cached; the empty statements
+// that differ from branch to branch keep them apart.
+template <typename F> __device__ __forceinline__ void either(bool nt, F &&f)
+{
+    if (nt) {
+        asm volatile("; streaming" ::: "memory");
+        f(std::true_type());
+        asm volatile("; streaming done" ::: "memory");
+    } else {
+        asm volatile("; cached" ::: "memory");
+        f(std::false_type());
+        asm volatile("; cached done" ::: "memory");
+    }
 }
 // one complex value (float2 or double2), cached
 template <typename T> __device__ __forceinline__ T gld(const T *p)

@@ -30,12 +30,13 @@ hipError_t ct_make_twiddles(int N, bool fp64, void *tw, hipStream_t s);
 bool ct_plan_step(int N, bool fp64, const XposeDesc &d, CtStep *step);
 hipError_t launch_ct_fused(const CtStep &step, const void *tw, const XposeDesc &d, int dir, const void *in, void *out,
                            double scale, CachePolicy policy, hipStream_t s);
+hipError_t launch_count(const XposeDesc &d, hipStream_t s);
 hipError_t launch_ct_rows(int N, bool fp64, const void *tw, int64_t nrows, int dir, const void *in, void *out,
                           double scale, CachePolicy policy, hipStream_t s);
 hipError_t launch_fft_xpose_generic(const FftDesc &f, const XposeDesc &d, bool fp64, int dir, const void *in,
                                     void *out, double scale, hipStream_t s);
 hipError_t launch_fft_mfma_xpose(int precision, int dir, int N, const void *twN, const XposeDesc &d, const void *in,
-                                 void *out, double scale, hipStream_t s);
+                                 void *out, double scale, bool nt_store, hipStream_t s);
 hipError_t launch_fft_mfma(int precision, int dir, int N, const void *twN, int64_t nrows, const void *in, void *out,
                            double scale, hipStream_t s);
 hipError_t launch_fft_rows(const FftDesc &d, bool fp64, int dir, const void *in, void *out, double scale,
@@ -390,16 +391,23 @@ int run_fused_step(fft_plan_impl *pl, int t, int nx, int dir, const void *src, v
 {
     const double scale = (dir > 0 && t == pl->M - 1) ? 1.0 / (double)pl->T : 1.0;
     const FftDesc &d = pl->fft[t];
-    if (pl->fuse_kind[t] == 1)
-        HIP_TRY(launch_ct_fused(pl->ct_step[t], d.tw, pl->xp[t], dir, src, dst, scale,
+    const XposeDesc &x = pl->xp[t];
+    if (pl->fuse_kind[t] == 1) {
+        HIP_TRY(launch_ct_fused(pl->ct_step[t], d.tw, x, dir, src, dst, scale,
                                 cache_policy(pl, t == nx - 1, pl->ct_step[t].whole), s),
                 "fused fft+transpose launch");
-    else if (pl->fuse_kind[t] == 3)
-        HIP_TRY(launch_fft_mfma_xpose(d.mfma, dir, d.N, d.tw, pl->xp[t], src, dst, scale, s),
+    } else if (pl->fuse_kind[t] == 3) {
+        HIP_TRY(launch_fft_mfma_xpose(d.mfma, dir, d.N, d.tw, x, src, dst, scale,
+                                      cache_policy(pl, t == nx - 1, x.Nv % 16 == 0).nt_store, s),
                 "fused mfma fft+transpose launch");
-    else
-        HIP_TRY(launch_fft_xpose_generic(d, pl->xp[t], pl->esz == 16, dir, src, dst, scale, s),
-                "fused fft+transpose launch");
+    } else {
+        // single points: the run-time-radix unit, its count apart (the unit
+        // adds to its counter, which nothing resets here)
+        XposeDesc y = x;
+        y.count = 0;
+        HIP_TRY(launch_fft_xpose_generic(d, y, pl->esz == 16, dir, src, dst, scale, s), "fused fft+transpose launch");
+        if (x.count) HIP_TRY(launch_count(x, s), "owner count launch");
+    }
     return FFTRW_OK;
 }
 
@@ -408,7 +416,7 @@ int run_pipeline(fft_plan_impl *pl, const void *in, void *out, hipStream_t s, in
     const int M = pl->M;
     const bool leave = (pl->flags & FFTRW_FLAG_LEAVE_PERMUTED) != 0;
     const int nx = leave ? M - 1 : M;
-    if (pl->counters) HIP_TRY(launch_zero_u64(pl->counters, pl->n_counters, s), "counter reset");
+    if (pl->counters && !pl->fused) HIP_TRY(launch_zero_u64(pl->counters, pl->n_counters, s), "counter reset");
     int nev = 0;
     auto mark = [&]() -> int {
         if (!pl->timing) return FFTRW_OK;
@@ -685,18 +693,20 @@ int plan_create(fft_plan_t *plan, int M, const int64_t *dims, int64_t P, const i
             }
         }
     }
-    // fusion of every FFT step with its transpose (the default): power-of-two
-    // rows of 16..512 (256 in FP64) whose work-group's run of consecutive
-    // v-values fits the v axis use the compile-time kernel; 2,3,5-smooth rows
-    // use the generic unit; steps of the split-precision form (256 and 512
-    // points) use the MFMA kernel
+    // fusion of every FFT step with its transpose (the default): rows of 2 and
+    // more points use the compile-time kernel of their length, single points
+    // the run-time-radix unit, steps of the split-precision form (256 and 512
+    // points) the MFMA kernel
     if (!(flags & (FFTRW_FLAG_SEPARATE | FFTRW_FLAG_STAGED)) && !generic_rows) {
         const bool fp64 = pl->esz == 16;
         const int nx = (flags & FFTRW_FLAG_LEAVE_PERMUTED) ? M - 1 : M;
         bool ok = true;
         for (int t = 0; t < nx && ok; ++t) {
             const FftDesc &d = pl->fft[t];
-            const bool ct_ok = d.ct && !d.mfma && ct_plan_step(d.N, fp64, pl->xp[t], &pl->ct_step[t]);
+            // (a plan of the split-precision form fuses with rows of up to 512
+            // points beside the MFMA kernel's)
+            const bool ct_ok = d.ct && !d.mfma && (pl->precision == FFTRW_PREC_NATIVE || d.N <= 512) &&
+                               ct_plan_step(d.N, fp64, pl->xp[t], &pl->ct_step[t]);
             const bool generic_ok = !d.ct && !d.mfma && d.N + 1 <= (fp64 ? 2048 : 4096);
             pl->fuse_kind[t] = d.mfma ? 3 : (ct_ok ? 1 : (generic_ok ? 2 : 0));
             ok = pl->fuse_kind[t] != 0;
@@ -805,7 +815,7 @@ int fft_plan_stats(fft_plan_t plan, int64_t *per_step, int64_t *moved)
             for (int t = 0; t < M; ++t) {
                 if (leave && t == M - 1) continue;
                 unsigned long long sum = 0;
-                for (int k = 0; k < kCountSlots; ++k) sum += h[(size_t)t * kCountBlock + (size_t)k * kCountStride];
+                for (int k = 0; k < kCountBlock; ++k) sum += h[(size_t)t * kCountBlock + (size_t)k];
                 moved[t] = (int64_t)sum;
             }
         }
@@ -841,7 +851,7 @@ int fft_plan_rowsplit_stats(fft_plan_t plan, int64_t *per_step, int64_t *moved)
                 return fail(FFTRW_E_DEVICE, "reading counters failed");
             for (int t = 0; t < M; ++t) {
                 unsigned long long sum = 0;
-                for (int k = 0; k < kCountSlots; ++k) sum += h[(size_t)t * kCountBlock + (size_t)k * kCountStride];
+                for (int k = 0; k < kCountBlock; ++k) sum += h[(size_t)t * kCountBlock + (size_t)k];
                 moved[t] = (int64_t)sum;
             }
         }

@@ -21,8 +21,6 @@
 
 #include <hip/hip_runtime.h>
 
-#include <type_traits>
-
 #include "cplx.hpp"
 #include "fft_ct_table.hpp"
 #include "fft_generic.hpp"
@@ -152,20 +150,18 @@ template <class P, int p> constexpr int ct_max_span()
 // LDS pitch of the rows' exchange buffers: odd, so that rows start on different banks
 template <class P> constexpr int ct_row_pitch() { return ct_max_span<P, P::NP - 1>() | 1; }
 
-// coordinates of batch slice g (innermost batch axis first) and its bases
-__device__ __forceinline__ void ct_slice(const XposeDesc &d, const CtShape &s, uint32_t g, int *c, int64_t *ab,
-                                         int64_t *bb)
+// bases of batch slice g (innermost batch axis first) in A and B
+__device__ __forceinline__ void ct_slice(const XposeDesc &d, const CtShape &s, uint32_t g, int64_t *ab, int64_t *bb)
 {
     int64_t a = 0, b = 0;
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
-        // (axes past nbat have size 1 and strides 0)
-        const uint32_t n = (uint32_t)d.bsize[i];
+        // (axes past nbat have size 0 and strides 0, and g is 0 by then)
         const uint32_t q = s.db[i](g);
-        c[i] = (int)(g - q * n);
+        const int c = (int)(g - q * (uint32_t)d.bsize[i]);
         g = q;
-        a += c[i] * d.ba[i];
-        b += c[i] * d.bb[i];
+        a += c * d.ba[i];
+        b += c * d.bb[i];
     }
     *ab = a;
     *bb = b;
@@ -301,22 +297,6 @@ template <bool NT, typename T> __device__ __forceinline__ void ct_st(T v, T *p)
         __builtin_nontemporal_store(v, p);
     else
         *p = v;
-}
-
-// Calls f<true>() or f<false>() by a uniform choice.  Of two branches that
-// differ in the kind of their loads alone the compiler makes one, cached; the
-// empty statements that differ from branch to branch keep them apart.
-template <typename F> __device__ __forceinline__ void ct_either(bool nt, F &&f)
-{
-    if (nt) {
-        asm volatile("; streaming" ::: "memory");
-        f(std::true_type());
-        asm volatile("; streaming done" ::: "memory");
-    } else {
-        asm volatile("; cached" ::: "memory");
-        f(std::false_type());
-        asm volatile("; cached done" ::: "memory");
-    }
 }
 
 // pass 0's inputs straight from the row in HBM
@@ -526,14 +506,19 @@ __device__ __forceinline__ void ct_store_runs(C *out, const C *lds, const CtShap
 // A work-group transforms rw rows along u (the last axis of layout A),
 // consecutive in v (the last axis of layout B), in each of G batch slices, and
 // writes layout B through an LDS block: every k of a slice becomes one run of
-// consecutive v.  Owner changes are counted per row (row_keep) while the loads
-// are in flight.
+// consecutive v.  The first ncount groups of the launch count the transpose's
+// owner changes instead (count_share).
 template <typename C, int N>
 __global__ void __launch_bounds__((CtPlan<C, N>::MAXNT))
-    ct_fused_kernel(const void *in_, void *out_, const XposeDesc d, const CtShape s, const void *tw_, double scale)
+    ct_fused_kernel(const void *in_, void *out_, const XposeDesc d, const CtShape s, const void *tw_, double scale,
+                    int ncount)
 {
     using P = CtPlan<C, N>;
     extern __shared__ __align__(16) unsigned char smem[];
+    if (blockIdx.x < (unsigned)ncount) {
+        count_share(d, blockIdx.x, ncount, reinterpret_cast<unsigned long long *>(smem));
+        return;
+    }
     C *lds = reinterpret_cast<C *>(smem);
     int64_t *bbase = reinterpret_cast<int64_t *>(smem + s.tab);
     int64_t *rowa = bbase + s.G;  // first element of every row (short rows)
@@ -542,7 +527,7 @@ __global__ void __launch_bounds__((CtPlan<C, N>::MAXNT))
     const C *__restrict__ tw = reinterpret_cast<const C *>(tw_);
     const int nth = P::L << s.lr;
 
-    uint32_t unit = blockIdx.x;
+    uint32_t unit = blockIdx.x - (unsigned)ncount;
     if (s.per_xcd) {
         // work-groups go to the 8 XCDs in turn; neighbouring units share the
         // cache lines at the ends of their runs
@@ -555,8 +540,7 @@ __global__ void __launch_bounds__((CtPlan<C, N>::MAXNT))
     const int nv = min(s.rw, (int)d.Nv - v0);
     const int ng = min(s.G, (int)(d.nslices - g0));
     int64_t abase0 = 0, bbase0 = 0;
-    int bc0[3] = {0, 0, 0};
-    if (s.G == 1) ct_slice(d, s, g0, bc0, &abase0, &bbase0);
+    if (s.G == 1) ct_slice(d, s, g0, &abase0, &bbase0);
 
     const int rho = threadIdx.x / P::L, lane = threadIdx.x % P::L;
     CtVals<P, 0, C> v;
@@ -570,16 +554,15 @@ __global__ void __launch_bounds__((CtPlan<C, N>::MAXNT))
         if (s.G > 1) {
             gi = rho / s.rw;
             r = rho - gi * s.rw;
-            int bc[3];
             int64_t bb;
             if (gi < ng) {
-                ct_slice(d, s, g0 + gi, bc, &ab, &bb);
+                ct_slice(d, s, g0 + gi, &ab, &bb);
                 if (r == 0 && lane == 0) bbase[gi] = bb;
             }
         }
         if (gi < ng && r < nv) {
             const C *src = in + ab + (v0 + r) * d.a_sv;
-            ct_either(s.nt_load, [&](auto nt) { ct_load_direct<P, nt.value, C>(v, src, lane); });
+            either(s.nt_load, [&](auto nt) { ct_load_direct<P, nt.value, C>(v, src, lane); });
         } else {
 #pragma unroll
             for (int e = 0; e < CtPass<P, 0>::IT * CtPass<P, 0>::R; ++e) v.x[e] = mk<C>(0, 0);
@@ -590,9 +573,8 @@ __global__ void __launch_bounds__((CtPlan<C, N>::MAXNT))
         if (s.G > 1) {
             if ((int)threadIdx.x < nrows) {
                 const int gi = threadIdx.x / (uint32_t)nv, r = threadIdx.x - gi * nv;
-                int bc[3];
                 int64_t ab, bb;
-                ct_slice(d, s, g0 + gi, bc, &ab, &bb);
+                ct_slice(d, s, g0 + gi, &ab, &bb);
                 rowa[threadIdx.x] = ab + (v0 + r) * d.a_sv;
                 if (r == 0) bbase[gi] = bb;
             }
@@ -600,22 +582,7 @@ __global__ void __launch_bounds__((CtPlan<C, N>::MAXNT))
         }
         const C *src = s.G > 1 ? in : in + abase0 + (int64_t)v0 * d.a_sv;
         const int64_t *tab = s.G > 1 ? rowa : nullptr;
-        ct_either(s.nt_load, [&](auto nt) { ct_load_staged<P, nt.value, C>(lds, src, d.a_sv, tab, nth, nrows); });
-    }
-    if (d.count && (int)(threadIdx.x & ~63u) < ng * nv) {
-        // owner changes, one row per thread; each wave publishes its sum at
-        // once (work left for the end would delay the group's exit)
-        int moved = 0;
-        if ((int)threadIdx.x < ng * nv) {
-            const int gi = threadIdx.x / (uint32_t)nv, r = threadIdx.x - gi * nv;
-            int bc[3] = {bc0[0], bc0[1], bc0[2]};
-            int64_t ab, bb;
-            if (s.G > 1) ct_slice(d, s, g0 + gi, bc, &ab, &bb);
-            moved = N - (int)row_keep(d, bc, v0 + r, 0, N);
-        }
-        for (int off = 32; off > 0; off >>= 1) moved += __shfl_xor(moved, off);
-        if ((threadIdx.x & 63) == 0 && moved)
-            atomicAdd(d.counter + (unit % kCountSlots) * kCountStride, (unsigned long long)moved);
+        either(s.nt_load, [&](auto nt) { ct_load_staged<P, nt.value, C>(lds, src, d.a_sv, tab, nth, nrows); });
     }
     if constexpr (!P::DIRECT) {
         __syncthreads();
@@ -664,13 +631,13 @@ __global__ void __launch_bounds__((CtPlan<C, N>::MAXNT))
     // aligned
     if constexpr (sizeof(C) == 8) {
         if (((d.Nv | s.rw) & 1) == 0 && s.lr > 0) {
-            ct_either(s.nt_store, [&](auto nt) {
+            either(s.nt_store, [&](auto nt) {
                 ct_store_runs<P, nt.value, 2, C>(out, lds, s, d.b_su, bbase, bbase0, v0, nv, ng);
             });
             return;
         }
     }
-    ct_either(s.nt_store, [&](auto nt) {
+    either(s.nt_store, [&](auto nt) {
         ct_store_runs<P, nt.value, 1, C>(out, lds, s, d.b_su, bbase, bbase0, v0, nv, ng);
     });
 }
@@ -697,13 +664,13 @@ __global__ void __launch_bounds__((CtPlan<C, N>::MAXNT))
     if constexpr (P::NP > 1) ct_load_tw<P, 1, C>(w1, lane, tw);
     if constexpr (P::DIRECT) {
         if (rho < here) {
-            ct_either(s.nt_load, [&](auto nt) { ct_load_direct<P, nt.value, C>(v, in + rho * N, lane); });
+            either(s.nt_load, [&](auto nt) { ct_load_direct<P, nt.value, C>(v, in + rho * N, lane); });
         } else {
 #pragma unroll
             for (int e = 0; e < CtPass<P, 0>::IT * CtPass<P, 0>::R; ++e) v.x[e] = mk<C>(0, 0);
         }
     } else {
-        ct_either(s.nt_load, [&](auto nt) { ct_load_staged<P, nt.value, C>(lds, in, N, nullptr, nth, here); });
+        either(s.nt_load, [&](auto nt) { ct_load_staged<P, nt.value, C>(lds, in, N, nullptr, nth, here); });
         __syncthreads();
         ct_read_row<P, 0, C>(v, row, lane);
         row_sync(P::L <= 64);
@@ -726,7 +693,7 @@ __global__ void __launch_bounds__((CtPlan<C, N>::MAXNT))
                 if constexpr (P::STORE_DIRECT) {
                     if (rho < here) {
                         V *p = reinterpret_cast<V *>(out + rho * N + j);
-                        ct_either(s.nt_store, [&](auto nt) {
+                        either(s.nt_store, [&](auto nt) {
 #pragma unroll
                             for (int i = 0; i < S::R; ++i)
                                 ct_st<nt.value>(V{y.x[m * S::R + i].x, y.x[m * S::R + i].y}, p + i * S::NB);
@@ -741,7 +708,7 @@ __global__ void __launch_bounds__((CtPlan<C, N>::MAXNT))
     });
     if constexpr (!P::STORE_DIRECT) {
         __syncthreads();
-        ct_either(s.nt_store, [&](auto nt) { ct_store_staged<P, nt.value, C>(out, lds, nth, here); });
+        either(s.nt_store, [&](auto nt) { ct_store_staged<P, nt.value, C>(out, lds, nth, here); });
     }
 }
 

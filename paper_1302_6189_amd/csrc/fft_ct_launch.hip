@@ -199,6 +199,19 @@ hipError_t ct_make_twiddles(int N, bool fp64, void *tw, hipStream_t s)
     return hipGetLastError();
 }
 
+// a transpose's owner changes alone
+__global__ void __launch_bounds__(kThreads) count_kernel(const XposeDesc d)
+{
+    __shared__ unsigned long long part[kThreads / 64];
+    count_share(d, blockIdx.x, gridDim.x, part);
+}
+
+hipError_t launch_count(const XposeDesc &d, hipStream_t s)
+{
+    hipLaunchKernelGGL(count_kernel, dim3(count_groups(d, kThreads)), dim3(kThreads), 0, s, d);
+    return hipGetLastError();
+}
+
 // the launch of a fused step, false if the kernel has no shape for it
 bool ct_plan_step(int N, bool fp64, const XposeDesc &d, CtStep *step)
 {
@@ -215,7 +228,9 @@ hipError_t launch_ct_fused(const CtStep &step, const void *tw, const XposeDesc &
     c.nt_store = policy.nt_store;
     c.inverse = dir > 0;
     c.do_scale = scale != 1.0;
-    hipLaunchKernelGGL(step.e->fused, dim3(step.grid), dim3(step.threads), step.lds, s, in, out, d, c, tw, scale);
+    const int ncount = d.count ? count_groups(d, step.threads) : 0;
+    hipLaunchKernelGGL(step.e->fused, dim3(step.grid + ncount), dim3(step.threads), step.lds, s, in, out, d, c, tw, scale,
+                       ncount);
     return hipGetLastError();
 }
 

@@ -63,7 +63,7 @@ struct CtShape {
     CtDiv dtv, db[3];       // divisions by tiles_v and by the batch axes' sizes
 };
 
-using CtFusedKernel = void (*)(const void *, void *, const XposeDesc, const CtShape, const void *, double);
+using CtFusedKernel = void (*)(const void *, void *, const XposeDesc, const CtShape, const void *, double, int);
 using CtRowsKernel = void (*)(const void *, void *, int64_t, const CtShape, const void *, double);
 
 struct CtEntry {

@@ -306,8 +306,7 @@ __global__ void __launch_bounds__(kThreads)
 // once both contractions have read it, so the 70 KB block is the only row
 // buffer and two work-groups fit a CU (8-row units, 64-byte runs, fit three
 // and ran 40% slower); a 256-point row goes through a per-wave buffer.  A resident grid walks the units, so the
-// split F16 operands (FP64 sin/cos) are built once per work-group.  Owner
-// changes are counted per row (tile_moved).
+// split F16 operands (FP64 sin/cos) are built once per work-group.
 constexpr int kMaxDevices = 64;  // devices whose resident grid size is cached
 
 constexpr int kMfmaRows = 16;
@@ -315,7 +314,7 @@ constexpr int kMfmaRows = 16;
 template <int PREC, int DIR, int R>
 __global__ void __launch_bounds__(kThreads)
     fft_mfma_xpose_kernel(const float2 *in, float2 *out, XposeDesc d, const float2 *__restrict__ twN, float scale,
-                          int do_scale)
+                          int do_scale, int nt_store, int ncount)
 {
     using PT = Parts<PREC>;
     using V = typename PT::V;
@@ -327,13 +326,17 @@ __global__ void __launch_bounds__(kThreads)
     __shared__ __align__(16) float2 xbuf[kCol ? 1 : kThreads / 64][kCol ? 1 : N];
     __shared__ float2 ybuf[kThreads / 64][16 * 17];
     __shared__ float2 stg[N * SR];
-    __shared__ int moved_wg;
 
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int g = lane >> 4;
     const int c = lane & 15;
     float2 *yb = ybuf[wave];
+    if (blockIdx.x < (unsigned)ncount) {
+        // owner changes, on groups of their own
+        count_share(d, blockIdx.x, ncount, reinterpret_cast<unsigned long long *>(stg));
+        return;
+    }
 
     // the F16 operands and twiddles are set up once; the resident grid then
     // walks the units u = blockIdx.x, + gridDim.x, ...
@@ -341,12 +344,10 @@ __global__ void __launch_bounds__(kThreads)
     dft16_operands<PT, DIR>(lane, a1, a2);
     float2 tw[4], twc[4];
     mfma_twiddles<R>(twN, lane, tw, twc);
-    if (threadIdx.x == 0) moved_wg = 0;
-    int moved = 0;
 
     const int64_t tiles_v = (d.Nv + RW - 1) / RW;
     const int64_t nunits = tiles_v * d.nslices;
-    for (int64_t unit = blockIdx.x; unit < nunits; unit += gridDim.x) {
+    for (int64_t unit = blockIdx.x - (unsigned)ncount; unit < nunits; unit += gridDim.x - (unsigned)ncount) {
         const int64_t tv = unit % tiles_v;
         const int64_t slice = unit / tiles_v;
         const int64_t v0 = tv * RW;
@@ -365,7 +366,6 @@ __global__ void __launch_bounds__(kThreads)
 #pragma unroll
             for (int q = 0; q < NQ; ++q) p[q] = __builtin_nontemporal_load(src + 64 * q + lane);
         }
-        if (d.count) moved += tile_moved(d, slice, 1, 0, N, v0, nv);
         for (; r < nv; r += kThreads / 64) {
             float2 *xb = kCol ? stg + r : xbuf[kCol ? 0 : wave];  // x[j] at xb[j XS]
             if constexpr (kCol) {
@@ -408,30 +408,28 @@ __global__ void __launch_bounds__(kThreads)
         const int npair = (nv + 1) / 2;
         const bool wide = (d.Nv & 1) == 0;
         float2 *dstb = out + bbase + v0;
-        for (int idx = threadIdx.x; idx < N * HP; idx += kThreads) {
-            const int rp = idx % HP;
-            const int k = idx / HP;
-            if (rp >= npair) continue;
-            const int r0 = 2 * rp;
-            float2 *q = dstb + (int64_t)k * d.b_su + r0;
-            const float2 a0 = stg[k * SR + r0];
-            if (r0 + 1 < nv && wide) {
-                const float2 a1v = stg[k * SR + r0 + 1];
-                mf4v w = {a0.x, a0.y, a1v.x, a1v.y};
-                __builtin_nontemporal_store(w, reinterpret_cast<mf4v *>(q));
-            } else {
-                xst(q, a0);
-                if (r0 + 1 < nv) xst(q + 1, stg[k * SR + r0 + 1]);
+        either(nt_store, [&](auto nt) {
+            for (int idx = threadIdx.x; idx < N * HP; idx += kThreads) {
+                const int rp = idx % HP;
+                const int k = idx / HP;
+                if (rp >= npair) continue;
+                const int r0 = 2 * rp;
+                float2 *q = dstb + (int64_t)k * d.b_su + r0;
+                const float2 a0 = stg[k * SR + r0];
+                if (r0 + 1 < nv && wide) {
+                    const float2 a1v = stg[k * SR + r0 + 1];
+                    const mf4v w = {a0.x, a0.y, a1v.x, a1v.y};
+                    if constexpr (nt.value)
+                        __builtin_nontemporal_store(w, reinterpret_cast<mf4v *>(q));
+                    else
+                        *reinterpret_cast<mf4v *>(q) = w;
+                } else {
+                    xst<nt.value>(q, a0);
+                    if (r0 + 1 < nv) xst<nt.value>(q + 1, stg[k * SR + r0 + 1]);
+                }
             }
-        }
+        });
         __syncthreads();  // the staging block is refilled by the next unit
-    }
-    if (d.count) {
-        for (int off = 32; off > 0; off >>= 1) moved += __shfl_xor(moved, off);
-        if ((threadIdx.x & 63) == 0 && moved) atomicAdd(&moved_wg, moved);
-        __syncthreads();
-        if (threadIdx.x == 0 && moved_wg)
-            atomicAdd(d.counter + (blockIdx.x % kCountSlots) * kCountStride, (unsigned long long)moved_wg);
     }
 }
 
@@ -460,7 +458,7 @@ hipError_t mfma_resident_grid(int *resident)
 
 template <int R>
 hipError_t launch_mfma_xpose_r(int precision, int dir, const void *twN, const XposeDesc &d, const void *in,
-                               void *out, double scale, hipStream_t s)
+                               void *out, double scale, bool nt_store, hipStream_t s)
 {
     constexpr int RW = kMfmaRows;
     const int64_t nunits = ((d.Nv + RW - 1) / RW) * d.nslices;
@@ -468,13 +466,14 @@ hipError_t launch_mfma_xpose_r(int precision, int dir, const void *twN, const Xp
     int resident = 0;
     if (hipError_t e = mfma_resident_grid<R>(&resident)) return e;
     const int ds = scale != 1.0;
-    dim3 grid((unsigned)std::min<int64_t>(nunits, resident)), block(kThreads);
+    const int ncount = d.count ? count_groups(d, kThreads) : 0;
+    dim3 grid((unsigned)std::min<int64_t>(nunits, resident) + ncount), block(kThreads);
     const float2 *i = (const float2 *)in;
     float2 *o = (float2 *)out;
     const float2 *t = (const float2 *)twN;
     const float sc = (float)scale;
 #define FFTRW_LAUNCH(P, D) \
-    hipLaunchKernelGGL((fft_mfma_xpose_kernel<P, D, R>), grid, block, 0, s, i, o, d, t, sc, ds)
+    hipLaunchKernelGGL((fft_mfma_xpose_kernel<P, D, R>), grid, block, 0, s, i, o, d, t, sc, ds, (int)nt_store, ncount)
     if (precision == kPrecF16) {
         if (dir < 0) FFTRW_LAUNCH(kPrecF16, -1); else FFTRW_LAUNCH(kPrecF16, 1);
     } else if (precision == kPrecBF16) {
@@ -489,10 +488,10 @@ hipError_t launch_mfma_xpose_r(int precision, int dir, const void *twN, const Xp
 }
 
 hipError_t launch_fft_mfma_xpose(int precision, int dir, int N, const void *twN, const XposeDesc &d, const void *in,
-                                 void *out, double scale, hipStream_t s)
+                                 void *out, double scale, bool nt_store, hipStream_t s)
 {
-    if (N == 256) return launch_mfma_xpose_r<1>(precision, dir, twN, d, in, out, scale, s);
-    if (N == 512) return launch_mfma_xpose_r<2>(precision, dir, twN, d, in, out, scale, s);
+    if (N == 256) return launch_mfma_xpose_r<1>(precision, dir, twN, d, in, out, scale, nt_store, s);
+    if (N == 512) return launch_mfma_xpose_r<2>(precision, dir, twN, d, in, out, scale, nt_store, s);
     return hipErrorInvalidValue;
 }
 

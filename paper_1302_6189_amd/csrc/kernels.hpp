@@ -8,10 +8,11 @@ namespace fftrw {
 constexpr int kMaxPasses = 12;
 constexpr int kThreads = 256;  // work-group size of every kernel here (4 waves of 64)
 
-// A device owner-change counter is kCountSlots partial sums on separate
-// 128-byte lines; work-group i adds to slot i % kCountSlots and readers sum
-// the slots.  One address shared by every work-group would serialise their
-// atomics across the chip's L2 slices.
+// A device owner-change counter is kCountBlock words whose sum is the count.
+// Kernels that add to it use kCountSlots partial sums on separate 128-byte
+// lines, work-group i slot i % kCountSlots (one address shared by every
+// work-group would serialise their atomics across the chip's L2 slices), and
+// need it zeroed; groups that count a whole transpose write every word.
 constexpr int kCountSlots = 32;
 constexpr int kCountStride = 16;  // 64-bit words between slots
 constexpr int kCountBlock = kCountSlots * kCountStride;

@@ -35,6 +35,7 @@ struct StagedStep {
     void *chunk_seg = nullptr;    // device int64[2 * chunks]: first/last segment of each exchange chunk
     int64_t seg_elems = 0;        // = the transpose's amount (points exchanged)
     int seg_axis = -1;            // natural axis along which segments run
+    int64_t seg_run = 0;          // extent of a representative (p, q) box along it
     StagedTileCfg pack, unpack;   // tilings of the two kernels
 };
 

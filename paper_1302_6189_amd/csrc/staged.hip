@@ -118,6 +118,7 @@ struct StagedTile {
     const RecvInfo *recv;
     const int2 *lrank;      // per (slice, u) line: rank_q at v = 0, step per v
     const PairSlot *pairs;  // D(p, q) of every pair that shares points
+    int nt_store;           // streaming (non-temporal) stores of the values
 };
 
 struct ExchangeArgs {
@@ -125,6 +126,7 @@ struct ExchangeArgs {
     const int64_t *chunk_seg;  // per chunk: first and last segment it touches
     int64_t nseg, total;
     unsigned long long *counter;
+    int nt_store;           // streaming (non-temporal) stores
 };
 
 // points of box B that precede coordinates c in the box's axis order
@@ -272,7 +274,8 @@ __device__ __forceinline__ void tile_pass(int lu, int lv, int lg, int nu, int nv
 
 // PACK:   src = layout A, dst = send array.
 // UNPACK: src = receive array, self_src = send array (kept segments), dst = layout B.
-template <typename C, bool PACK, int LR, int LW>
+// NTL: streaming loads of the values.
+template <typename C, bool PACK, int LR, int LW, bool NTL>
 __global__ void __launch_bounds__(kThreads)
     staged_tile_kernel(const C *__restrict__ src, const C *__restrict__ self_src, C *__restrict__ dst, StagedTile a)
 {
@@ -357,7 +360,7 @@ __global__ void __launch_bounds__(kThreads)
         const int a_sv = (int)d.a_sv;
         tile_pass<LR>(lu, lv, lg, nu, nv, ng, [&](int j, int g, int iv, int iu) {
             at[j] = g * SG + iv * SV + iu;
-            val[j] = xld(src + (gbase[g] + (int)(v0 + iv) * a_sv + (int)u0 + iu));
+            val[j] = xld<NTL>(src + (gbase[g] + (int)(v0 + iv) * a_sv + (int)u0 + iu));
         });
     }
     {
@@ -448,7 +451,7 @@ __global__ void __launch_bounds__(kThreads)
             } else {
                 off = rb[k] + rk - (p > keep_src ? kp[k] : 0);
             }
-            val[j] = (uint32_t)off < (uint32_t)a.T ? xld(from + off) : mk<C>(0, 0);
+            val[j] = (uint32_t)off < (uint32_t)a.T ? xld<NTL>(from + off) : mk<C>(0, 0);
         });
     }
 #pragma unroll
@@ -456,26 +459,28 @@ __global__ void __launch_bounds__(kThreads)
         if (at[j] >= 0) tile[at[j]] = val[j];
     __syncthreads();
     // write
-    if (PACK) {
-        if (dense) {
-            tile_pass<LW>(lu, lv, lg, nu, nv, ng, [&](int, int g, int iv, int iu) {
-                const int k = g * KU + iu;
-                const int off = pt[own_a[g * KV + iv] * nq + own_b[k]] + r0[k] + iv * wv[k];
-                if ((uint32_t)off < (uint32_t)a.T) xst(dst + off, tile[g * SG + iv * SV + iu]);
-            });
+    either(a.nt_store, [&](auto nt) {
+        if (PACK) {
+            if (dense) {
+                tile_pass<LW>(lu, lv, lg, nu, nv, ng, [&](int, int g, int iv, int iu) {
+                    const int k = g * KU + iu;
+                    const int off = pt[own_a[g * KV + iv] * nq + own_b[k]] + r0[k] + iv * wv[k];
+                    if ((uint32_t)off < (uint32_t)a.T) xst<nt.value>(dst + off, tile[g * SG + iv * SV + iu]);
+                });
+            } else {
+                tile_pass<LW>(lu, lv, lg, nu, nv, ng, [&](int, int g, int iv, int iu) {
+                    const int k = g * KU + iu;
+                    const int off = pair_offset(a, own_a[g * KV + iv], own_b[k]) + r0[k] + iv * wv[k];
+                    if ((uint32_t)off < (uint32_t)a.T) xst<nt.value>(dst + off, tile[g * SG + iv * SV + iu]);
+                });
+            }
         } else {
+            const int b_su = (int)d.b_su;
             tile_pass<LW>(lu, lv, lg, nu, nv, ng, [&](int, int g, int iv, int iu) {
-                const int k = g * KU + iu;
-                const int off = pair_offset(a, own_a[g * KV + iv], own_b[k]) + r0[k] + iv * wv[k];
-                if ((uint32_t)off < (uint32_t)a.T) xst(dst + off, tile[g * SG + iv * SV + iu]);
+                xst<nt.value>(dst + (gbase[g] + (int)(u0 + iu) * b_su + (int)v0 + iv), tile[g * SG + iv * SV + iu]);
             });
         }
-    } else {
-        const int b_su = (int)d.b_su;
-        tile_pass<LW>(lu, lv, lg, nu, nv, ng, [&](int, int g, int iv, int iu) {
-            xst(dst + (gbase[g] + (int)(u0 + iu) * b_su + (int)v0 + iv), tile[g * SG + iv * SV + iu]);
-        });
-    }
+    });
 }
 
 // Plan time: for every (slice, u) line, in the slice numbering of the tiles,
@@ -553,14 +558,16 @@ __global__ void __launch_bounds__(kThreads)
             const int i = threadIdx.x + j * kThreads;
             if (i < n) v[j] = xld(from + i);
         }
+        either(a.nt_store, [&](auto nt) {
 #pragma unroll
-        for (int j = 0; j < kChunkItems; ++j) {
-            const int i = threadIdx.x + j * kThreads;
-            if (i < n) {
-                xst(to + i, v[j]);
-                ++copied;
+            for (int j = 0; j < kChunkItems; ++j) {
+                const int i = threadIdx.x + j * kThreads;
+                if (i < n) {
+                    xst<nt.value>(to + i, v[j]);
+                    ++copied;
+                }
             }
-        }
+        });
     } else {
         // several segments: their descriptors in LDS when few enough, so a
         // point's copy needs one global load (its value), not two
@@ -594,13 +601,15 @@ __global__ void __launch_bounds__(kThreads)
                 }
             }
         }
+        either(a.nt_store, [&](auto nt) {
 #pragma unroll
-        for (int j = 0; j < kChunkItems; ++j) {
-            if (to[j] >= 0) {
-                xst(recv + to[j], v[j]);
-                ++copied;
+            for (int j = 0; j < kChunkItems; ++j) {
+                if (to[j] >= 0) {
+                    xst<nt.value>(recv + to[j], v[j]);
+                    ++copied;
+                }
             }
-        }
+        });
     }
     __syncthreads();
     for (int off = 32; off > 0; off >>= 1) copied += __shfl_xor(copied, off);
@@ -656,8 +665,9 @@ void fill_boxes(const std::vector<Box> &boxes, const int *perm, int M, RankBox *
 
 // The natural axis along which (p, q) segments run: the innermost axis, in A's
 // order, that spans more than one value in a representative pair box (the
-// largest piece of a middle process's largest range box).
-int segment_axis(const Layout &a, const Layout &b, int M)
+// largest piece of a middle process's largest range box); *run is the box's
+// extent along it.
+int segment_axis(const Layout &a, const Layout &b, int M, i64 *run)
 {
     const std::vector<Box> bx = range_boxes(a, a.P / 2);
     size_t big = 0;
@@ -676,8 +686,12 @@ int segment_axis(const Layout &a, const Layout &b, int M)
     });
     for (int i = M - 1; i >= 0; --i) {
         const int ax = a.perm[i];
-        if (best.hi[ax] > best.lo[ax]) return ax;
+        if (best.hi[ax] > best.lo[ax]) {
+            *run = best.hi[ax] - best.lo[ax] + 1;
+            return ax;
+        }
     }
+    *run = 1;
     return a.perm[M - 1];
 }
 
@@ -892,7 +906,7 @@ int staged_build(fft_plan_impl *pl, int t)
     st.seg_elems = moved;
     st.nbq = nbq;
     st.pair_lg = lg;
-    st.seg_axis = segment_axis(a, b, M);
+    st.seg_axis = segment_axis(a, b, M, &st.seg_run);
     st.pack = make_tile(pl, t, st.seg_axis, true);
     st.unpack = make_tile(pl, t, st.seg_axis, false);
     for (const StagedTileCfg *c : {&st.pack, &st.unpack}) {
@@ -975,24 +989,52 @@ StagedTile tile_args(const fft_plan_impl *pl, const StagedStep &st, const Staged
     return g;
 }
 
+// Streaming or cached values.  Segments whose runs end inside a 128-byte line
+// are written and read in parts of lines, which only the caches join; whole
+// runs follow the other passes' rule (stores cached while the arrays are near
+// the Infinity Cache's size, loads cached below 64 MB).  Staged forward
+// transforms, all streaming / this rule: 200^3 N_p = 64 609 / 415 us, 320^3
+// N_p = 100 2057 / 1390, 256^3 N_p = 512 652 / 608; all cached at 512^3,
+// N_p = 4096: 5184 us against 4871 streaming.
+void staged_policy(const fft_plan_impl *pl, const StagedStep &st, const XposeDesc &d, CachePolicy *segments,
+                   CachePolicy *rows)
+{
+    const size_t bytes = (size_t)pl->T * pl->esz;
+    const bool large = bytes > ((size_t)400 << 20);
+    const bool whole = (size_t)st.seg_run * pl->esz % 128 == 0;
+    *segments = {whole && bytes > ((size_t)64 << 20), whole && large};
+    *rows = {bytes > ((size_t)64 << 20), large && (size_t)d.Nv * pl->esz % 128 == 0};
+}
+
 // part 0: pack (layout A -> send array), 1: exchange (only segments between
 // different processes), 2: unpack (receive array and kept segments -> layout B)
 template <typename C>
 hipError_t launch_staged(const fft_plan_impl *pl, const StagedStep &st, int part, const void *in, void *out,
                          hipStream_t s, int t)
 {
+    CachePolicy segments, rows;
+    staged_policy(pl, st, st.pack.d, &segments, &rows);
     if (part == 0) {
-        const StagedTile g = tile_args(pl, st, st.pack);
+        StagedTile g = tile_args(pl, st, st.pack);
+        g.nt_store = segments.nt_store;
         const size_t lds = tile_lds(g.lu, g.lv, g.lg, sizeof(C), true).total;
         const unsigned n = (unsigned)(g.d.tiles_u * g.d.tiles_v * g.d.tiles_g);
         const C *i = (const C *)in;
         C *o = (C *)pl->send;
+        auto go = [&](auto lw) {
+            if (rows.nt_load)
+                hipLaunchKernelGGL((staged_tile_kernel<C, true, 0, decltype(lw)::value, true>), dim3(n), dim3(kThreads),
+                                   lds, s, i, i, o, g);
+            else
+                hipLaunchKernelGGL((staged_tile_kernel<C, true, 0, decltype(lw)::value, false>), dim3(n),
+                                   dim3(kThreads), lds, s, i, i, o, g);
+        };
         if (g.lane_w == 0)
-            hipLaunchKernelGGL((staged_tile_kernel<C, true, 0, 0>), dim3(n), dim3(kThreads), lds, s, i, i, o, g);
+            go(std::integral_constant<int, 0>());
         else if (g.lane_w == 1)
-            hipLaunchKernelGGL((staged_tile_kernel<C, true, 0, 1>), dim3(n), dim3(kThreads), lds, s, i, i, o, g);
+            go(std::integral_constant<int, 1>());
         else
-            hipLaunchKernelGGL((staged_tile_kernel<C, true, 0, 2>), dim3(n), dim3(kThreads), lds, s, i, i, o, g);
+            go(std::integral_constant<int, 2>());
         return hipGetLastError();
     }
     if (part == 1) {
@@ -1003,22 +1045,32 @@ hipError_t launch_staged(const fft_plan_impl *pl, const StagedStep &st, int part
         x.nseg = st.nseg;
         x.total = st.seg_elems;
         x.counter = pl->counters + (size_t)t * kCountBlock;
+        x.nt_store = segments.nt_store;
         const unsigned xb = (unsigned)((st.seg_elems + kChunk - 1) / kChunk);
         hipLaunchKernelGGL(exchange_kernel<C>, dim3(xb), dim3(kThreads), 0, s, (const C *)pl->send, (C *)pl->recv,
                            x);
         return hipGetLastError();
     }
-    const StagedTile g = tile_args(pl, st, st.unpack);
+    StagedTile g = tile_args(pl, st, st.unpack);
+    g.nt_store = rows.nt_store;
     const size_t lds = tile_lds(g.lu, g.lv, g.lg, sizeof(C), false).total;
     const unsigned n = (unsigned)(g.d.tiles_u * g.d.tiles_v * g.d.tiles_g);
     const C *r = (const C *)pl->recv, *sd = (const C *)pl->send;
     C *o = (C *)out;
+    auto go = [&](auto lr) {
+        if (segments.nt_load)
+            hipLaunchKernelGGL((staged_tile_kernel<C, false, decltype(lr)::value, 1, true>), dim3(n), dim3(kThreads), lds,
+                               s, r, sd, o, g);
+        else
+            hipLaunchKernelGGL((staged_tile_kernel<C, false, decltype(lr)::value, 1, false>), dim3(n), dim3(kThreads),
+                               lds, s, r, sd, o, g);
+    };
     if (g.lane_r == 0)
-        hipLaunchKernelGGL((staged_tile_kernel<C, false, 0, 1>), dim3(n), dim3(kThreads), lds, s, r, sd, o, g);
+        go(std::integral_constant<int, 0>());
     else if (g.lane_r == 1)
-        hipLaunchKernelGGL((staged_tile_kernel<C, false, 1, 1>), dim3(n), dim3(kThreads), lds, s, r, sd, o, g);
+        go(std::integral_constant<int, 1>());
     else
-        hipLaunchKernelGGL((staged_tile_kernel<C, false, 2, 1>), dim3(n), dim3(kThreads), lds, s, r, sd, o, g);
+        go(std::integral_constant<int, 2>());
     return hipGetLastError();
 }
 

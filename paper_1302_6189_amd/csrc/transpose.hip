@@ -5,11 +5,11 @@
 
 namespace fftrw {
 
-template <typename C, int VU, int VV>
+template <typename C, int VU, int VV, bool NT>
 __global__ void __launch_bounds__(kThreads) xpose_kernel(const C *__restrict__ in, C *__restrict__ out, XposeDesc d)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    xpose_tile<C, VU, VV>(in, out, d, blockIdx.x, smem_raw);
+    xpose_tile<C, VU, VV, NT>(in, out, d, blockIdx.x, smem_raw);
 }
 
 size_t xpose_lds_bytes(const XposeDesc &d, size_t esz) { return xpose_tile_bytes(d, esz) + 16; }
@@ -23,21 +23,28 @@ hipError_t launch_xpose(const XposeDesc &d, size_t esz, const void *in, void *ou
     // 16-byte accesses for complex64 along an even fast axis
     const bool vu = esz == 8 && d.Nu % 2 == 0 && d.TU >= 2;
     const bool vv = esz == 8 && d.Nv % 2 == 0 && d.TV >= 2;
-    if (esz == 8) {
-        const float2 *i = (const float2 *)in;
-        float2 *o = (float2 *)out;
-        if (vu && vv)
-            hipLaunchKernelGGL((xpose_kernel<float2, 2, 2>), grid, block, lds, s, i, o, d);
-        else if (vu)
-            hipLaunchKernelGGL((xpose_kernel<float2, 2, 1>), grid, block, lds, s, i, o, d);
-        else if (vv)
-            hipLaunchKernelGGL((xpose_kernel<float2, 1, 2>), grid, block, lds, s, i, o, d);
+    // stores stream only in whole 128-byte lines, whose parts the caches join
+    const bool nt = (d.Nv * (int64_t)esz) % 128 == 0 && (d.TV * esz) % 128 == 0;
+    auto go = [&](auto c, auto u, auto v) {
+        using C = decltype(c);
+        constexpr int VU = decltype(u)::value, VV = decltype(v)::value;
+        if (nt)
+            hipLaunchKernelGGL((xpose_kernel<C, VU, VV, true>), grid, block, lds, s, (const C *)in, (C *)out, d);
         else
-            hipLaunchKernelGGL((xpose_kernel<float2, 1, 1>), grid, block, lds, s, i, o, d);
-    } else {
-        hipLaunchKernelGGL((xpose_kernel<double2, 1, 1>), grid, block, lds, s, (const double2 *)in,
-                           (double2 *)out, d);
-    }
+            hipLaunchKernelGGL((xpose_kernel<C, VU, VV, false>), grid, block, lds, s, (const C *)in, (C *)out, d);
+    };
+    using One = std::integral_constant<int, 1>;
+    using Two = std::integral_constant<int, 2>;
+    if (esz != 8)
+        go(double2(), One(), One());
+    else if (vu && vv)
+        go(float2(), Two(), Two());
+    else if (vu)
+        go(float2(), Two(), One());
+    else if (vv)
+        go(float2(), One(), Two());
+    else
+        go(float2(), One(), One());
     return hipGetLastError();
 }
 

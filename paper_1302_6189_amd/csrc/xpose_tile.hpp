@@ -37,9 +37,11 @@ typedef float xf4 __attribute__((ext_vector_type(4)));
 typedef float xf2 __attribute__((ext_vector_type(2)));
 typedef double xd2 __attribute__((ext_vector_type(2)));
 
-template <typename C> __device__ __forceinline__ C xld(const C *p)
+template <bool NT = true, typename C> __device__ __forceinline__ C xld(const C *p)
 {
-    if constexpr (sizeof(C) == 8) {
+    if constexpr (!NT) {
+        return gld(p);
+    } else if constexpr (sizeof(C) == 8) {
         xf2 w = gld_nt(reinterpret_cast<const xf2 *>(p));
         return mk<C>(w.x, w.y);
     } else {
@@ -47,15 +49,14 @@ template <typename C> __device__ __forceinline__ C xld(const C *p)
         return mk<C>(w.x, w.y);
     }
 }
-template <typename C> __device__ __forceinline__ void xst(C *p, C v)
+template <bool NT = true, typename C> __device__ __forceinline__ void xst(C *p, C v)
 {
-    if constexpr (sizeof(C) == 8) {
-        xf2 w = {v.x, v.y};
-        gst_nt(w, reinterpret_cast<xf2 *>(p));
-    } else {
-        xd2 w = {v.x, v.y};
-        gst_nt(w, reinterpret_cast<xd2 *>(p));
-    }
+    using V = typename std::conditional<sizeof(C) == 8, xf2, xd2>::type;
+    const V w = {v.x, v.y};
+    if constexpr (NT)
+        gst_nt(w, reinterpret_cast<V *>(p));
+    else
+        gst(w, reinterpret_cast<V *>(p));
 }
 
 __device__ __forceinline__ int64_t owner_of_row(int64_t r, int64_t P, int64_t R, bool narrow)
@@ -84,59 +85,106 @@ __device__ __forceinline__ void slice_coords(const XposeDesc &d, int64_t s, int 
     *bb = b;
 }
 
-// Points of the row (batch coordinates c, v) with u in [u0, u0 + nu) that keep
-// their owner.  Both row indices are affine in u: B's grows with u when u is
-// one of B's leading axes, A's only at level M.  Owners are monotone in the
-// row index, so the row is a sequence of pieces of constant A owner o, and
-// inside a piece the u whose B row lies in o's range form an interval.
-__device__ __forceinline__ int64_t row_keep(const XposeDesc &d, const int *c, int64_t v, int64_t u0, int64_t nu)
+// Row indices of a batch slice's points in A and B, affine in u and v: A's
+// grows with u only at level M, B's with v only there.
+struct SliceRows {
+    int64_t ra0 = 0, wau = 0, wav = 0;
+    int64_t rb0 = 0, wbu = 0, wbv = 0;
+};
+
+__device__ __forceinline__ SliceRows slice_rows(const XposeDesc &d, const int *c)
 {
-    const bool narrow = d.owner32 != 0;
-    int64_t ra0 = 0, wau = 0, rb0 = 0, wbu = 0;
+    SliceRows r;
     for (int j = 0; j < d.ka; ++j) {
         const int src = d.srca[j];
         if (src == 4)
-            wau = d.wa[j];
+            r.wau = d.wa[j];
+        else if (src == 3)
+            r.wav = d.wa[j];
         else
-            ra0 += (src == 3 ? v : (int64_t)c[src]) * d.wa[j];
+            r.ra0 += (int64_t)c[src] * d.wa[j];
     }
     for (int j = 0; j < d.kb; ++j) {
         const int src = d.srcb[j];
         if (src == 4)
-            wbu = d.wb[j];
+            r.wbu = d.wb[j];
+        else if (src == 3)
+            r.wbv = d.wb[j];
         else
-            rb0 += (src == 3 ? v : (int64_t)c[src]) * d.wb[j];
+            r.rb0 += (int64_t)c[src] * d.wb[j];
     }
-    // floor(x / y) for x >= 0, y > 0, and ceil(x / w) for w > 0.  When
-    // R P < 2^32 for both layouts (narrow) every operand below is under 2^32,
-    // so 32-bit divisions suffice.
-    auto fdiv = [narrow](int64_t x, int64_t y) -> int64_t {
-        return narrow ? (int64_t)((uint32_t)x / (uint32_t)y) : x / y;
-    };
-    auto cdiv = [&](int64_t x, int64_t w) -> int64_t {
-        if (x < 0) return -fdiv(-x, w);
-        const int64_t q = fdiv(x, w);
-        return q + (q * w != x ? 1 : 0);
-    };
-    // u in [a, b) whose B row lies in the range of process o
-    auto keep_b = [&](int64_t o, int64_t a, int64_t b) -> int64_t {
-        if (wbu == 0) return owner_of_row(rb0, d.P, d.Rb, narrow) == o ? b - a : 0;
-        const int64_t lo = fdiv(d.Rb * o, d.P) - rb0, hi = fdiv(d.Rb * (o + 1), d.P) - rb0;
-        const int64_t k0 = max<int64_t>(a, cdiv(lo, wbu)), k1 = min<int64_t>(b, cdiv(hi, wbu));
-        return max<int64_t>(0, k1 - k0);
-    };
-    if (wau == 0) {
+    return r;
+}
+
+// floor(x / y) for x >= 0, y > 0, and ceil(x / w) for w > 0.  When R P < 2^32
+// for both layouts (narrow) every operand is under 2^32, so 32-bit divisions
+// suffice.
+__device__ __forceinline__ int64_t owner_fdiv(int64_t x, int64_t y, bool narrow)
+{
+    return narrow ? (int64_t)((uint32_t)x / (uint32_t)y) : x / y;
+}
+__device__ __forceinline__ int64_t owner_cdiv(int64_t x, int64_t w, bool narrow)
+{
+    if (x < 0) return -owner_fdiv(-x, w, narrow);
+    const int64_t q = owner_fdiv(x, w, narrow);
+    return q + (q * w != x ? 1 : 0);
+}
+
+// u in [a, b) whose row rb0 + u wbu of B lies in the range of process o
+__device__ __forceinline__ int64_t keep_in_b(const XposeDesc &d, int64_t rb0, int64_t wbu, int64_t o, int64_t a,
+                                             int64_t b)
+{
+    const bool narrow = d.owner32 != 0;
+    if (wbu == 0) return owner_of_row(rb0, d.P, d.Rb, narrow) == o ? b - a : 0;
+    const int64_t lo = owner_fdiv(d.Rb * o, d.P, narrow) - rb0, hi = owner_fdiv(d.Rb * (o + 1), d.P, narrow) - rb0;
+    const int64_t k0 = max<int64_t>(a, owner_cdiv(lo, wbu, narrow)), k1 = min<int64_t>(b, owner_cdiv(hi, wbu, narrow));
+    return max<int64_t>(0, k1 - k0);
+}
+
+// Points of the row (batch coordinates c, v) with u in [u0, u0 + nu) that keep
+// their owner.  Owners are monotone in the row index, so the row is a
+// sequence of pieces of constant A owner o, and inside a piece the u whose B
+// row lies in o's range form an interval.
+__device__ __forceinline__ int64_t row_keep(const XposeDesc &d, const SliceRows &r, int64_t v, int64_t u0, int64_t nu)
+{
+    const bool narrow = d.owner32 != 0;
+    const int64_t ra0 = r.ra0 + v * r.wav, rb0 = r.rb0 + v * r.wbv;
+    if (r.wau == 0) {
         int64_t o = owner_of_row(ra0, d.P, d.Ra, narrow);
         if (d.mu) o = d.mu[o];
-        return keep_b(o, u0, u0 + nu);
+        return keep_in_b(d, rb0, r.wbu, o, u0, u0 + nu);
     }
     int64_t keep = 0;
     for (int64_t u = u0, end = u0 + nu; u < end;) {
-        const int64_t oa = owner_of_row(ra0 + u * wau, d.P, d.Ra, narrow);
+        const int64_t oa = owner_of_row(ra0 + u * r.wau, d.P, d.Ra, narrow);
         // first u past this piece: A row reaches the start of range oa + 1
-        const int64_t next = min<int64_t>(end, cdiv(fdiv(d.Ra * (oa + 1), d.P) - ra0, wau));
-        keep += keep_b(d.mu ? (int64_t)d.mu[oa] : oa, u, next);
+        const int64_t next =
+            min<int64_t>(end, owner_cdiv(owner_fdiv(d.Ra * (oa + 1), d.P, narrow) - ra0, r.wau, narrow));
+        keep += keep_in_b(d, rb0, r.wbu, d.mu ? (int64_t)d.mu[oa] : oa, u, next);
         u = next;
+    }
+    return keep;
+}
+
+// Points of the rows v in [v0, v1) of a batch slice that keep their owner.
+// Below level M A's owner is constant along u and B's along v, so the rows
+// come in pieces of constant A owner whose intervals of u are the same.
+__device__ __forceinline__ int64_t rows_keep(const XposeDesc &d, const int *c, int64_t v0, int64_t v1)
+{
+    const bool narrow = d.owner32 != 0;
+    const SliceRows r = slice_rows(d, c);
+    int64_t keep = 0;
+    if (r.wau != 0 || r.wbv != 0) {
+        for (int64_t v = v0; v < v1; ++v) keep += row_keep(d, r, v, 0, d.Nu);
+        return keep;
+    }
+    for (int64_t v = v0; v < v1;) {
+        const int64_t oa = owner_of_row(r.ra0 + v * r.wav, d.P, d.Ra, narrow);
+        int64_t next = v1;
+        if (r.wav != 0)
+            next = min<int64_t>(v1, owner_cdiv(owner_fdiv(d.Ra * (oa + 1), d.P, narrow) - r.ra0, r.wav, narrow));
+        keep += (next - v) * keep_in_b(d, r.rb0, r.wbu, d.mu ? (int64_t)d.mu[oa] : oa, 0, d.Nu);
+        v = next;
     }
     return keep;
 }
@@ -152,9 +200,54 @@ __device__ __forceinline__ int tile_moved(const XposeDesc &d, int64_t g0, int ng
         int c[3];
         int64_t ab, bb;
         slice_coords(d, g0 + g, c, &ab, &bb);
-        moved += nu - (int)row_keep(d, c, v0 + iv, u0, nu);
+        moved += nu - (int)row_keep(d, slice_rows(d, c), v0 + iv, u0, nu);
     }
     return moved;
+}
+
+// Owner changes of a whole transpose, counted by `groups` work-groups: items of
+// slices, or parts of slices when there are few.  The count depends on the
+// decompositions alone: on groups of their own it costs the transform nothing
+// (512^3: 1.2% when the row groups counted in front of their first barrier),
+// and short kernels no reset launch (32^3 complex128 18.9 -> 13.8 us), as
+// every word of the counter is written.
+__host__ __device__ inline uint32_t count_chunks(const XposeDesc &d)
+{
+    const uint32_t n = d.nslices < 8192 ? 8192u / (uint32_t)d.nslices : 1u;
+    return n < (uint32_t)d.Nv ? n : (uint32_t)d.Nv;
+}
+// two items a thread
+inline int count_groups(const XposeDesc &d, int threads)
+{
+    const int64_t n = d.nslices * count_chunks(d) / (2 * threads);
+    return (int)(n < 16 ? 16 : n > kCountBlock ? kCountBlock : (n + 7) / 8 * 8);
+}
+
+// The share of group `group`; `part` holds one word per wave.
+__device__ __forceinline__ void count_share(const XposeDesc &d, int group, int groups, unsigned long long *part)
+{
+    const uint32_t Nv = (uint32_t)d.Nv, ns = (uint32_t)d.nslices, chunks = count_chunks(d);
+    const uint32_t per = (Nv + chunks - 1) / chunks;
+    unsigned long long moved = 0;
+    for (uint64_t i = (uint64_t)group * blockDim.x + threadIdx.x; i < (uint64_t)ns * chunks;
+         i += (uint64_t)groups * blockDim.x) {
+        // (chunks > 1 only below 8192 slices: 32 bits hold the product)
+        const uint32_t g = chunks == 1 ? (uint32_t)i : (uint32_t)i / chunks;
+        const uint32_t v0 = ((uint32_t)i - g * chunks) * per, v1 = min(Nv, v0 + per);
+        if (v0 >= v1) continue;
+        int c[3];
+        int64_t ab, bb;
+        slice_coords(d, g, c, &ab, &bb);
+        moved += (unsigned long long)((int64_t)(v1 - v0) * d.Nu - rows_keep(d, c, v0, v1));
+    }
+    for (int off = 32; off > 0; off >>= 1) moved += __shfl_xor(moved, off);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = moved;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (unsigned w = 1; w < blockDim.x / 64; ++w) moved += part[w];
+    // the group's word, and zeros to the other words of its residue
+    for (int w = group + threadIdx.x * groups; w < kCountBlock; w += blockDim.x * groups)
+        d.counter[w] = w == group ? moved : 0;
 }
 
 // LDS bytes of a tile, 16-byte aligned; launchers reserve 16 more bytes
@@ -166,8 +259,8 @@ __host__ __device__ inline size_t xpose_tile_bytes(const XposeDesc &d, size_t es
 }
 
 // One tile of the transpose: tile index t (u fastest, then v, then slices);
-// smem holds the tile.
-template <typename C, int VU, int VV>
+// smem holds the tile.  NT: streaming stores.
+template <typename C, int VU, int VV, bool NT = true>
 __device__ __forceinline__ void xpose_tile(const C *__restrict__ in, C *__restrict__ out, const XposeDesc &d,
                                            uint32_t tile_index, unsigned char *smem)
 {
@@ -286,9 +379,12 @@ __device__ __forceinline__ void xpose_tile(const C *__restrict__ in, C *__restri
                 if (dst[j]) {
                     if constexpr (VV == 2) {
                         const xf4 w = {val[j][0].x, val[j][0].y, val[j][1].x, val[j][1].y};
-                        gst_nt(w, reinterpret_cast<xf4 *>(dst[j]));
+                        if constexpr (NT)
+                            gst_nt(w, reinterpret_cast<xf4 *>(dst[j]));
+                        else
+                            gst(w, reinterpret_cast<xf4 *>(dst[j]));
                     } else {
-                        xst(dst[j], val[j][0]);
+                        xst<NT>(dst[j], val[j][0]);
                     }
                 }
         }
