@@ -542,10 +542,13 @@ int plan_create(fft_plan_t *plan, int M, const int64_t *dims, int64_t P, const i
             return fail(st);
         }
     }
-    // analytic amounts (and relabellings for the matched reading)
+    // analytic amounts (and relabellings for the matched reading).  A plan on
+    // an arena lives for one exec whose caller cannot ask for its amounts, and
+    // its ownership is literal: with their O(P) count a 64^3 call kept the host
+    // 21.2 us at N_p = 16 and 26.1 at 64, without it 18.1 at either
     pl->analytic.assign(M, 0);
     pl->mu.assign(M, {});
-    for (int t = 0; t < M; ++t) {
+    for (int t = 0; t < M && !arena; ++t) {
         st = transpose_amount(pl->lay[t], pl->lay[t + 1], pl->ownership, &pl->analytic[t], &pl->mu[t]);
         if (!st) {
             free_plan(pl);
