@@ -5,21 +5,34 @@
 // units -- a block of rows of one FFT step, or a tile of one transpose --
 // grouped into stage levels: level s holds stage s of every item that has
 // one.  One grid of work-groups, sized to stay resident, sweeps the levels:
-// inside a level units are taken from the level's atomic counter, a few
-// consecutive units per claim.  A work-group leaving a level adds the number
-// of units it completed there to the level's done counter (after a release
-// at device scope, issued by one wave for the group) and waits until the
-// counter holds every unit of the level (then acquires, so data written on
-// one XCD is seen on the others), which keeps every item's FFT -> transpose
-// -> FFT order.  Counting units rather than arrivals means no
-// work-group waits for one that has not started: a unit is only ever claimed
-// by a running work-group, and a level is left only once all its units are
-// claimed, so the wait ends whether or not the whole grid is resident
-// (another kernel may hold part of the device).  Waiting polls a
-// device-coherent counter without invalidating caches, and every wait is
+// units are taken from one atomic counter, a few consecutive units per claim,
+// level after level.  A work-group leaves a level once its next claim is of a
+// later one; the last group to leave on an XCD writes that XCD's L2 back
+// (a release at device scope) and adds the units its groups completed to the
+// level's done counter, and whoever completes that counter opens the next
+// level, for which the groups wait on copies of one word (then acquire, so
+// data written on one XCD is seen on the others).  This keeps every item's
+// FFT -> transpose -> FFT order.  Counting units rather than arrivals means
+// no work-group waits for one that has not started: a unit is only ever
+// claimed by a running work-group, and a level is left only once all its
+// units are claimed, so the wait ends whether or not the whole grid is
+// resident (another kernel may hold part of the device).  Waiting polls a
+// device-coherent word without invalidating caches, and every wait is
 // bounded by the real-time clock: past the bound the work-group adds one to
 // a sticky time-out count and goes on, so the grid always drains and the
 // host can refuse the result.
+//
+// What the levels cost: same-address atomics take 11.5 ns each, and 1024
+// groups that each release or acquire at device scope 7.5 us, so a level's
+// end can cost a small batch more than its units.  With one release per XCD
+// instead of per group, no claim made in vain, no more groups than units and
+// the waiters off the counters' lines, one 96^3 transform takes 64 us instead
+// of 224, sixteen 64^3 153 instead of 378, 32 items of 9 x 10^3 to 4 x 10^6
+// points 572 instead of 854 and 256 of them 3.44 ms instead of 3.69
+// (complex64).  Eight claim counters, one per XCD, take the small ones
+// further (53 and 125 us) and the large ones back (590 us, 3.59 ms): the
+// search for units left elsewhere costs every unit registers and
+// instructions.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -64,11 +77,29 @@ struct BatchTask {
     int64_t unit0, nunits;  // unit0 counts from the start of the task's level
 };
 
-// zeroed before every launch: one claim counter and one done counter per level
-struct BatchCounters {
-    unsigned long long next[kMaxStages];
-    unsigned long long done[kMaxStages];
+// A claim takes 2^kClaimLog units, and single units for a level's last
+// kClaimTail per work-group.
+constexpr int kClaimLog = 2;
+constexpr int kClaimTail = 4;
+
+// zeroed before every launch, one per level: the claim counter (level 0's
+// serves every level), a counter of completed units, copies of the word that
+// opens the next level, and a word per XCD (bits 63:48 groups that entered
+// the level, 47:32 groups that left it, 31:0 their completed units not yet in
+// `done`), each on a 128-byte line of its own
+constexpr int kCtrLine = 16;     // 64-bit words per line
+constexpr int kOpenCopies = 32;
+constexpr int kMaxXcds = 16;
+struct BatchLevelCtr {
+    unsigned long long next[kCtrLine];
+    unsigned long long done[kCtrLine];
+    unsigned long long open[kOpenCopies][kCtrLine];
+    unsigned long long xcd[kMaxXcds][kCtrLine];
 };
+constexpr unsigned long long kEntered = 1ull << 48, kLeft = 1ull << 32;
+
+// the XCD this wave runs on: bits 3:0 of hardware register 20 (XCC_ID)
+__device__ __forceinline__ int xcd_id() { return __builtin_amdgcn_s_getreg(20 | (0 << 6) | ((4 - 1) << 11)); }
 
 // task starts of one level held in LDS for the per-unit search
 constexpr int kLevelTasksLds = 256;
@@ -76,11 +107,6 @@ constexpr int kLevelTasksLds = 256;
 // s_waitcnt operand: vector memory count 0 (bits 3:0 and 15:14), the export
 // and LDS/scalar counts at their maxima (bits 6:4 and 11:8)
 constexpr int kWaitVmcnt0 = 0x0F70;
-
-// units per claim of the level counter, and the level's last units claimed
-// one at a time (this many per work-group of the grid)
-constexpr int kClaimUnits = 3;
-constexpr int kClaimTail = 4;
 
 // real-time clock ticks (100 MHz) a work-group may wait at one barrier
 constexpr unsigned long long kWaitTicks = 200000000ull;
@@ -116,51 +142,60 @@ template <int DIR, bool TW_LDS, bool LEAN>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(LEAN ? 4 : (DIR > 0 ? 3 : 1))))
     batch_kernel(const BatchItemDev *__restrict__ items, const BatchTask *__restrict__ tasks,
                  const int *__restrict__ level_task0, const int64_t *__restrict__ level_units, int nlevels,
-                 BatchCounters *ctr, unsigned long long *timeouts, unsigned long long wait_ticks)
+                 BatchLevelCtr *ctr, unsigned long long *timeouts, unsigned long long wait_ticks)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ int64_t s_unit0[kLevelTasksLds];
-    __shared__ int64_t s_unit;
-    __shared__ int s_task, s_end;
+    __shared__ int s_unit0[kLevelTasksLds];
+    __shared__ int s_unit, s_task, s_end;
+    unsigned pending = 0;     // thread 0: its claim in flight
+    unsigned claims0 = 0;     // claims of the levels before this one
+    const int xcd = xcd_id();
+    if (threadIdx.x == 0) {
+        atomicAdd(&ctr[0].xcd[xcd][0], kEntered);
+        pending = claim(&ctr[0].next[0]);
+    }
     for (int lv = 0; lv < nlevels; ++lv) {
         const int64_t nunits = level_units[lv];
         const int t0 = level_task0[lv], t1 = level_task0[lv + 1];
         // the level's task starts, searched in LDS when they fit
         const bool in_lds = t1 - t0 <= kLevelTasksLds;
         if (in_lds)
-            for (int i = threadIdx.x; i < t1 - t0; i += kThreads) s_unit0[i] = tasks[t0 + i].unit0;
+            for (int i = threadIdx.x; i < t1 - t0; i += kThreads) s_unit0[i] = (int)tasks[t0 + i].unit0;
         __syncthreads();
-        // Thread 0 claims units from the level's counter and finds each one's
-        // task (a binary search over the level's task starts, skipped while
-        // the units stay in one task).  A claim takes a chunk of kClaimUnits
-        // consecutive units, and single units for the level's last
-        // kClaimTail x grid, so that few atomics reach the one counter and
-        // the level still ends evenly.  A unit's successor is handed to the
-        // work-group (s_unit, s_task) in the middle of the unit, once the
+        // Thread 0 claims units and finds each one's task (a binary search
+        // over the level's task starts, skipped while the units stay in one
+        // task).  A claim takes a chunk of consecutive units, and a single
+        // unit for the level's last kClaimTail x grid, so that few atomics
+        // reach the counter (they take 11.5 ns each whoever issues them) and
+        // the level still ends evenly.  The levels' claims are numbered
+        // through: a claim past a level's end is one of the next level, kept
+        // over the barrier, so that no claim is made in vain and none is
+        // waited for when a level starts.  A unit's successor is handed to
+        // the work-group (s_unit, s_task) in the middle of the unit, once the
         // unit's own row loads have arrived, and a new chunk is claimed when
         // the last unit of the current one starts: loads, stores and atomics
         // count on one wait counter in issue order, so reading a claim at
         // the next unit's start would also wait for this unit's stores.
-        // (a level has fewer than 2^31 units, and claims stop one chunk past
-        // its end per work-group, so unit numbers fit in 32 bits)
+        // (a level has fewer than 2^31 units and the launch, with one claim
+        // past its end per work-group, fewer than 2^32 claims)
         const int nu32 = (int)nunits;
         const int tail = min(nu32, (int)gridDim.x * kClaimTail);
-        const int nchunk = (nu32 - tail) / kClaimUnits;  // chunks of kClaimUnits
-        const int head = nchunk * kClaimUnits;
+        const unsigned nchunk = (unsigned)(nu32 - tail) >> kClaimLog;
+        const unsigned head = nchunk << kClaimLog;
         // Thread 0 keeps the unit being run and its task in s_unit and s_task
         // (which the work-group reads), the end of its chunk in s_end, and
         // the claim in flight in a register.
-        unsigned pending = 0, ndone = 0;
+        unsigned ndone = 0;
         // thread 0: publish unit `cur` of chunk end `end`, its task searched
         // from task index `task` (counted from t0) on
         auto publish_unit = [&](int cur, int end, int task) {
             const int last = t1 - t0 - 1;
             if (cur < nu32 && task < last &&
-                cur >= (in_lds ? s_unit0[task + 1] : tasks[t0 + task + 1].unit0)) {
+                cur >= (in_lds ? s_unit0[task + 1] : (int)tasks[t0 + task + 1].unit0)) {
                 int lo = task + 1, hi = last;
                 while (lo < hi) {
                     const int mid = (lo + hi + 1) >> 1;
-                    if ((in_lds ? s_unit0[mid] : tasks[t0 + mid].unit0) <= cur)
+                    if ((in_lds ? s_unit0[mid] : (int)tasks[t0 + mid].unit0) <= cur)
                         lo = mid;
                     else
                         hi = mid - 1;
@@ -171,33 +206,33 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(L
             s_end = end;
             s_task = t0 + task;
         };
-        // thread 0: the first unit of claimed chunk c
-        auto publish_chunk = [&](unsigned c, int task) {
-            const int ci = (int)min(c, (unsigned)nu32);  // past the end: a unit >= nunits
-            const int cur = ci < nchunk ? ci * kClaimUnits : min(head + (ci - nchunk), nu32);
-            publish_unit(cur, ci < nchunk ? cur + kClaimUnits : cur + 1, task);
+        // thread 0: the first unit of the claim in flight, or unit nunits
+        auto publish_chunk = [&](int task) {
+            const unsigned c = pending - claims0;
+            const bool whole = c < nchunk;
+            const unsigned cur = whole ? c << kClaimLog : min(head + (c - nchunk), (unsigned)nu32);
+            publish_unit((int)cur, (int)(cur + (whole ? 1u << kClaimLog : 1u)), task);
         };
         auto publish = [&]() {
             if (threadIdx.x == 0) {
-                const int cur = (int)s_unit, end = s_end, task = s_task - t0;
+                const int cur = s_unit, end = s_end, task = s_task - t0;
                 if (cur + 1 < end)
                     publish_unit(cur + 1, end, task);
                 else
-                    publish_chunk(pending, task);
+                    publish_chunk(task);
             }
         };
-        if (threadIdx.x == 0) publish_chunk(claim(&ctr->next[lv]), 0);
+        if (threadIdx.x == 0) publish_chunk(0);
         __syncthreads();
         for (;;) {
             // every unit function synchronises the work-group before it calls
             // publish (and non-fused units are preceded by a barrier), so these
             // reads are done before thread 0 overwrites the values
-            const int64_t u = s_unit;
-            const int lo = s_task;
-            if (u >= nunits) break;
+            const int u = s_unit, lo = s_task;
+            if (u >= nu32) break;
             if (threadIdx.x == 0) {
                 ++ndone;
-                if (u + 1 >= s_end) pending = claim(&ctr->next[lv]);
+                if (u + 1 >= s_end) pending = claim(&ctr[0].next[0]);
             }
             const BatchTask tk = tasks[lo];
             const BatchItemDev &it = items[tk.item];
@@ -244,27 +279,47 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(L
             }
         }
         if (lv + 1 == nlevels) break;
+        claims0 += nchunk + ((unsigned)nu32 - head);
         // Level barrier: publish the units this group completed, wait for
         // all.  Every wave first waits until its own stores have completed
         // (they are then in the L2; a workgroup-scope release does not wait
         // for them); the agent-scope fences are issued by thread 0's wave
-        // alone: its release writes back the L2 (whatever wave wrote the
-        // lines) before the count is published, and its acquire invalidates
-        // the L2 and this CU's L1, which the group's other waves read
-        // through after the second barrier.
+        // alone: a release writes back the L2 (whatever wave of the XCD wrote
+        // the lines) before the count is published, and the acquire
+        // invalidates the L2 and this CU's L1, which the group's other waves
+        // read through after the second barrier.  The group that finds the
+        // XCD's entered and left counts equal takes the units counted there;
+        // a group that enters later finds them equal again when it leaves and
+        // takes its own.
         __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
         __syncthreads();
         if (threadIdx.x == 0) {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-            const unsigned long long target = (unsigned long long)nunits;
-            if (ndone) atomicAdd(&ctr->done[lv], (unsigned long long)ndone);
+            atomicAdd(&ctr[lv + 1].xcd[xcd][0], kEntered);
+            unsigned long long *mine = &ctr[lv].xcd[xcd][0];
+            const unsigned long long now = atomicAdd(mine, kLeft + ndone) + kLeft + ndone;
+            bool open = nunits == 0;
+            if ((now >> 48) == ((now >> 32) & 0xffff)) {
+                const unsigned long long n = atomicAnd(mine, ~0xffffffffull) & 0xffffffffull;
+                if (n) {
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                    if (atomicAdd(&ctr[lv].done[0], n) + n == (unsigned long long)nunits) {
+                        // the level's last units: every XCD's stores are in
+                        // memory before its count, the counts before this
+                        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "agent");
+                        for (int i = 0; i < kOpenCopies; ++i)
+                            __hip_atomic_store(&ctr[lv].open[i][0], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        open = true;
+                    }
+                }
+            }
+            const unsigned long long *word = &ctr[lv].open[blockIdx.x % kOpenCopies][0];
             const unsigned long long w0 = wall_clock64();
-            while (__hip_atomic_load(&ctr->done[lv], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
+            while (!open && !__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
                 if (wall_clock64() - w0 > wait_ticks) {
                     atomicAdd(timeouts, 1ull);
                     break;
                 }
-                __builtin_amdgcn_s_sleep(10);
+                __builtin_amdgcn_s_sleep(4);
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         }
@@ -295,7 +350,7 @@ struct fft_batch_impl {
     std::vector<BatchTask> h_tasks;
     BatchItemDev *d_items = nullptr;
     BatchTask *d_tasks = nullptr;
-    unsigned long long *d_ctr = nullptr;  // BatchCounters, then moved[sum of M_i]
+    unsigned long long *d_ctr = nullptr;  // a BatchLevelCtr per level, then moved[sum of M_i]
     unsigned long long *d_timeouts = nullptr;  // sticky count of timed-out waits (never reset)
     bool timed_out = false;               // a stats call has seen d_timeouts != 0
     unsigned long long wait_ticks = kWaitTicks;  // bound of one level wait (real-time clock ticks)
@@ -347,7 +402,7 @@ int batch_enqueue(fft_batch_impl *b, int dir, hipStream_t s)
     hipLaunchKernelGGL(batch_reset_kernel, dim3((unsigned)((nctr + 255) / 256)), dim3(256), 0, s, b->d_ctr, nctr);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return batch_fail_hip(e, "batch reset launch");
-    BatchCounters *ctr = reinterpret_cast<BatchCounters *>(b->d_ctr);
+    BatchLevelCtr *ctr = reinterpret_cast<BatchLevelCtr *>(b->d_ctr);
     const int nl = (int)b->level_units.size();
 #define FFTRW_LAUNCH(D, T, L)                                                                                   \
     hipLaunchKernelGGL((batch_kernel<D, T, L>), dim3(b->grid), dim3(kThreads), b->lds, s, b->d_items, b->d_tasks, \
@@ -569,7 +624,7 @@ int fft_batch_plan(fft_batch_t *out, int n, const fft_item_desc *items, int prec
         }
     }
     b->moved_off.resize(n);
-    b->nctr = (int64_t)(sizeof(BatchCounters) / sizeof(unsigned long long));
+    b->nctr = (int64_t)(b->level_units.size() * sizeof(BatchLevelCtr) / sizeof(unsigned long long));
     for (int i = 0; i < n; ++i) {
         b->moved_off[i] = b->nctr;
         b->nctr += (int64_t)b->h_items[i].M * kCountBlock;
@@ -587,7 +642,9 @@ int fft_batch_plan(fft_batch_t *out, int n, const fft_item_desc *items, int prec
         batch_free(b);
         return e != hipSuccess ? batch_fail_hip(e, "occupancy query") : fail(FFTRW_E_DEVICE, "kernel does not fit");
     }
-    b->grid = per_cu * ncu;
+    // no more groups than a level has units: every group claims past its end
+    b->grid = (int)std::min<int64_t>((int64_t)per_cu * ncu,
+                                     *std::max_element(b->level_units.begin(), b->level_units.end()));
     e = hipMalloc(&b->d_items, sizeof(BatchItemDev) * (size_t)n);
     if (e == hipSuccess) e = hipMalloc(&b->d_tasks, sizeof(BatchTask) * b->h_tasks.size());
     if (e == hipSuccess) e = hipMalloc(&b->d_ctr, sizeof(unsigned long long) * (size_t)b->nctr);
