@@ -242,7 +242,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(L
             float2 *dst = batch_buf(it, it.dst[st]);
             if constexpr (LEAN) {
                 const bool last = st == it.M - 1;
-                fft_xpose_unit<float2, DIR, TW_LDS, true, true>(src, dst, it.fft[st], it.xp[st], it.frw[st], it.fg[st],
+                fft_xpose_unit<float2, DIR, TW_LDS, true, true, true>(src, dst, it.fft[st], it.xp[st], it.frw[st], it.fg[st],
                                                                 local,
                                                                 DIR > 0 && last ? it.inv_scale : 1.f, DIR > 0 && last,
                                                                 smem, publish);
@@ -250,7 +250,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(L
             }
             if (it.fused && st < it.nx) {
                 const bool last = st == it.M - 1;
-                fft_xpose_unit<float2, DIR, TW_LDS>(src, dst, it.fft[st], it.xp[st], it.frw[st], it.fg[st], local,
+                fft_xpose_unit<float2, DIR, TW_LDS, false, false, true>(src, dst, it.fft[st], it.xp[st], it.frw[st], it.fg[st], local,
                                                     DIR > 0 && last ? it.inv_scale : 1.f, DIR > 0 && last, smem,
                                                     publish);
                 continue;

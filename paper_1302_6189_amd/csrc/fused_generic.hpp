@@ -120,7 +120,7 @@ template <typename C> __device__ __forceinline__ const C *at_off32(const C *base
 // loads of one trip before it reuses their registers on the next.  The owner
 // changes of the unit's rows are counted while the loads are in flight:
 // every thread with rows to count (threadIdx.x < ng nv) has loads too.
-template <int W, bool OFF32, typename C>
+template <int W, bool OFF32, bool NT, typename C>
 __device__ __forceinline__ void load_unit_rows(const C *__restrict__ in, C *lds, const FftDesc &f,
                                                const XposeDesc &d, const int64_t *abase, int S, int rw, int nv,
                                                int ng, int64_t g0, int64_t v0, int &moved)
@@ -142,11 +142,15 @@ __device__ __forceinline__ void load_unit_rows(const C *__restrict__ in, C *lds,
             const C *p = OFF32 ? at_off32(in, (uint32_t)abase[gi] + (uint32_t)(v0 + r) * (uint32_t)d.a_sv + c * W)
                                : in + abase[gi] + (v0 + r) * d.a_sv + c * W;
             if constexpr (W == 2) {
-                const xf4 w = gld_nt(reinterpret_cast<const xf4 *>(p));
+                xf4 w;
+                if constexpr (NT)
+                    w = gld_nt(reinterpret_cast<const xf4 *>(p));
+                else
+                    w = *(const __attribute__((address_space(1))) xf4 *)p;
                 val[j][0] = mk<C>(w.x, w.y);
                 val[j][1] = mk<C>(w.z, w.w);
             } else {
-                val[j][0] = xld(p);
+                val[j][0] = xld<NT>(p);
             }
             // c < NW and r < nv before the step, dc < NW and drr < nv: each
             // wraps at most once
@@ -180,7 +184,7 @@ __device__ __forceinline__ void load_unit_rows(const C *__restrict__ in, C *lds,
 // u = k, v = v0 + r).  Group e = (gi N + k) nv / W + r / W, W consecutive v
 // per access (W = 2: 16-byte stores of complex64, nv and every run start
 // even).
-template <int W, bool OFF32, typename C>
+template <int W, bool OFF32, bool NT, typename C>
 __device__ __forceinline__ void store_unit_runs(C *__restrict__ out, const C *lds, const XposeDesc &d,
                                                 const int64_t *bbase, int N, int S, int rw, int nv, int ng,
                                                 int64_t v0, typename RealOf<C>::type scale, bool do_scale)
@@ -201,9 +205,12 @@ __device__ __forceinline__ void store_unit_runs(C *__restrict__ out, const C *ld
                      : out + bbase[gi] + (int64_t)k * d.b_su + v0 + r * W;
         if constexpr (W == 2) {
             const xf4 w = {q[0].x, q[0].y, q[1].x, q[1].y};
-            gst_nt(w, reinterpret_cast<xf4 *>(p));
+            if constexpr (NT)
+                gst_nt(w, reinterpret_cast<xf4 *>(p));
+            else
+                gst(w, reinterpret_cast<xf4 *>(p));
         } else {
-            xst(p, q[0]);
+            xst<NT>(p, q[0]);
         }
         r += dr;
         gi += dg;
@@ -228,10 +235,20 @@ struct NoHook {
 // and sized the LDS block with it).  LEAN: the step's radices are 2, 3, 4 and
 // 5 only (the caller made sure), so the larger passes are not compiled in.
 // OFF32: `in` and `out` each hold fewer than 2^32 bytes (the caller made
-// sure), and HBM addresses are formed from 32-bit offsets.  hook() runs once the unit's rows are in LDS, after a barrier that every
+// sure), and HBM addresses are formed from 32-bit offsets.  CACHED (the
+// batch): cached loads, and streaming stores only of whole 128-byte lines.
+// The runs of uneven sizes rarely are whole lines, and parts of lines that
+// stream past the L2 reach memory apart; the next level also finds small
+// items in the Infinity Cache.  256 items of 9 x 10^3 to 4 x 10^6 points
+// 3.44 -> 2.97 ms, 2 x 512^3 (runs of 32 bytes) 9.7 -> 5.8, 4 x 288x240x250
+// 1.13 -> 0.96; whole lines alone gain nothing either way (96^3 64 us, 67
+// with cached stores; 8 x 160^3 475 -> 479 us), and a small batch of odd
+// lengths loses (2 x 81x125x75 91 -> 96 us: its lines are still in the L2
+// when the level's end writes it back).  hook() runs once the unit's rows are in LDS, after a barrier that every
 // thread passed after entering the unit; no HBM access of the unit's is in
 // flight then except the owner-count atomics.
-template <typename C, int DIR, bool TW_LDS, bool LEAN = false, bool OFF32 = false, typename Hook = NoHook>
+template <typename C, int DIR, bool TW_LDS, bool LEAN = false, bool OFF32 = false, bool CACHED = false,
+          typename Hook = NoHook>
 __device__ __forceinline__ void fft_xpose_unit(const C *__restrict__ in, C *__restrict__ out, const FftDesc &f,
                                                const XposeDesc &d, int rw, int G, int64_t unit,
                                                typename RealOf<C>::type scale, bool do_scale, unsigned char *smem,
@@ -270,12 +287,12 @@ __device__ __forceinline__ void fft_xpose_unit(const C *__restrict__ in, C *__re
     int moved = 0;
     if constexpr (sizeof(C) == 8) {
         if (N % 2 == 0) {
-            load_unit_rows<2, OFF32>(in, lds, f, d, abase, S, rw, nv, ng, g0, v0, moved);
+            load_unit_rows<2, OFF32, !CACHED>(in, lds, f, d, abase, S, rw, nv, ng, g0, v0, moved);
         } else {
-            load_unit_rows<1, OFF32>(in, lds, f, d, abase, S, rw, nv, ng, g0, v0, moved);
+            load_unit_rows<1, OFF32, !CACHED>(in, lds, f, d, abase, S, rw, nv, ng, g0, v0, moved);
         }
     } else {
-        load_unit_rows<1, OFF32>(in, lds, f, d, abase, S, rw, nv, ng, g0, v0, moved);
+        load_unit_rows<1, OFF32, !CACHED>(in, lds, f, d, abase, S, rw, nv, ng, g0, v0, moved);
     }
     hook();
     if constexpr (TW_LDS) {
@@ -325,12 +342,20 @@ __device__ __forceinline__ void fft_xpose_unit(const C *__restrict__ in, C *__re
     // (complex64: every run then starts on an even element)
     if constexpr (sizeof(C) == 8) {
         if (d.Nv % 2 == 0 && rw % 2 == 0) {
-            store_unit_runs<2, OFF32>(out, lds, d, bbase, N, S, rw, nv, ng, v0, scale, do_scale);
+            // whole 128-byte lines only: their streaming stores need no
+            // merging in the L2
+            if constexpr (CACHED)
+                either(d.Nv % 16 == 0 && rw % 16 == 0 && ((uintptr_t)out & 127) == 0, [&](auto nt) {
+                    store_unit_runs<2, OFF32, decltype(nt)::value>(out, lds, d, bbase, N, S, rw, nv, ng, v0, scale,
+                                                                   do_scale);
+                });
+            else
+                store_unit_runs<2, OFF32, true>(out, lds, d, bbase, N, S, rw, nv, ng, v0, scale, do_scale);
         } else {
-            store_unit_runs<1, OFF32>(out, lds, d, bbase, N, S, rw, nv, ng, v0, scale, do_scale);
+            store_unit_runs<1, OFF32, !CACHED>(out, lds, d, bbase, N, S, rw, nv, ng, v0, scale, do_scale);
         }
     } else {
-        store_unit_runs<1, OFF32>(out, lds, d, bbase, N, S, rw, nv, ng, v0, scale, do_scale);
+        store_unit_runs<1, OFF32, !CACHED>(out, lds, d, bbase, N, S, rw, nv, ng, v0, scale, do_scale);
     }
     __syncthreads();  // the LDS block may be reused by the caller's next unit
 }
