@@ -38,6 +38,7 @@
 #include <algorithm>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
 #include <string>
 #include <vector>
 
@@ -134,7 +135,7 @@ __device__ __forceinline__ float2 *batch_buf(const BatchItemDev &it, int kind)
 // The inverse (whose last stage also scales) is held to three waves per SIMD
 // (at most 168 VGPRs; it needs one more otherwise, which would leave two).
 // The forward fits without the hint and runs 1% faster without it.
-// LEAN: every stage of every item is a fused unit with radices 2, 3, 4 and 5
+// LEAN: every stage of every item is a fused unit with radices 2 to 6 and 8
 // only, and every item's buffers hold fewer than 2^32 bytes (32-bit offsets);
 // without the other stage kernels and the larger passes the kernel fits four
 // waves per SIMD.
@@ -242,7 +243,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(L
             float2 *dst = batch_buf(it, it.dst[st]);
             if constexpr (LEAN) {
                 const bool last = st == it.M - 1;
-                fft_xpose_unit<float2, DIR, TW_LDS, true, true, true>(src, dst, it.fft[st], it.xp[st], it.frw[st], it.fg[st],
+                fft_xpose_unit<float2, DIR, TW_LDS, kRadBatch, true, true>(src, dst, it.fft[st], it.xp[st], it.frw[st], it.fg[st],
                                                                 local,
                                                                 DIR > 0 && last ? it.inv_scale : 1.f, DIR > 0 && last,
                                                                 smem, publish);
@@ -250,7 +251,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(L
             }
             if (it.fused && st < it.nx) {
                 const bool last = st == it.M - 1;
-                fft_xpose_unit<float2, DIR, TW_LDS, false, false, true>(src, dst, it.fft[st], it.xp[st], it.frw[st], it.fg[st], local,
+                fft_xpose_unit<float2, DIR, TW_LDS, kRadBatch | kRadRows, false, true>(src, dst, it.fft[st], it.xp[st], it.frw[st], it.fg[st], local,
                                                     DIR > 0 && last ? it.inv_scale : 1.f, DIR > 0 && last, smem,
                                                     publish);
                 continue;
@@ -260,14 +261,14 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(L
             publish();
             if (it.fused) {
                 const bool last = st == it.M - 1;
-                fft_rows_block<float2, DIR>(src, dst, it.fft[st], local, DIR > 0 && last ? it.inv_scale : 1.f,
+                fft_rows_block<float2, DIR, false, kRadBatch | kRadRows>(src, dst, it.fft[st], local, DIR > 0 && last ? it.inv_scale : 1.f,
                                             DIR > 0 && last, reinterpret_cast<float2 *>(smem));
                 continue;
             }
             const int t = st >> 1;
             if ((st & 1) == 0) {
                 const bool last = t == it.M - 1;
-                fft_rows_block<float2, DIR>(src, dst, it.fft[t], local, DIR > 0 && last ? it.inv_scale : 1.f,
+                fft_rows_block<float2, DIR, false, kRadBatch | kRadRows>(src, dst, it.fft[t], local, DIR > 0 && last ? it.inv_scale : 1.f,
                                             DIR > 0 && last, reinterpret_cast<float2 *>(smem));
             } else {
                 switch (it.xv[t]) {
@@ -341,6 +342,7 @@ namespace fftrw {
 int plan_create(fft_plan_t *plan, int M, const int64_t *dims, int64_t P, const int8_t *order, int dtype,
                 int precision, unsigned flags, bool generic_rows, const TuneTable *tune, DevArena *arena);
 void plan_free(fft_plan_t plan);
+int factor_radices(int64_t n, int *rad);
 
 struct fft_batch_impl {
     int n = 0;
@@ -370,10 +372,43 @@ struct fft_batch_impl {
     bool tuned = false;  // a matching autotuner cache was applied
     bool any_fused = false;
     bool tw_lds = false;  // fused units stage their twiddle tables in LDS
-    bool lean = false;    // every stage a fused unit of radices 2..5 (batch_kernel's LEAN form)
+    bool lean = false;    // every stage a fused unit of radices 2 to 6 and 8 (batch_kernel's LEAN form)
 };
 
 namespace {
+
+// Radices of a batch's step of built-in order: of 2..6 and 8 the fewest
+// passes, then the smallest sum, those with fewer factors 2 first (a first
+// pass of radix r stores with a stride of r values, and strides of many
+// factors 2 meet on the LDS banks).  A lane holds 16 to 20 values whatever
+// the radix, so 6 and 8 cost the LEAN kernel no wave: 256 uneven items 2.97
+// -> 2.90 ms, 4 x 256^3 1.06 -> 0.92, sixteen 64^3 152 -> 134 us (64 x 60^3
+// 237 -> 240).  With 9 and 10 as well it spills and takes 3.09 ms.
+int batch_radices(i64 n, int *rad)
+{
+    int best[kMaxPasses], nbest = kMaxPasses + 1, sbest = 0, cur[kMaxPasses];
+    std::function<void(i64, int, int, int)> go = [&](i64 left, int np, int sum, int top) {
+        if (left == 1) {
+            if (np < nbest || (np == nbest && sum < sbest)) {
+                nbest = np;
+                sbest = sum;
+                std::copy(cur, cur + np, best);
+            }
+            return;
+        }
+        if (np + 1 > nbest || np == kMaxPasses) return;
+        for (int r : {8, 6, 5, 4, 3, 2})
+            if (r <= top && left % r == 0) {
+                cur[np] = r;
+                go(left / r, np + 1, sum + r, r);
+            }
+    };
+    go(n, 0, 0, 8);
+    auto twos = [](int r) { return r % 8 == 0 ? 3 : r % 4 == 0 ? 2 : r % 2 == 0 ? 1 : 0; };
+    std::sort(best, best + nbest, [&](int a, int b) { return twos(a) != twos(b) ? twos(a) < twos(b) : a > b; });
+    std::copy(best, best + nbest, rad);
+    return nbest;
+}
 
 int batch_fail_hip(hipError_t e, const char *what)
 {
@@ -589,13 +624,13 @@ int fft_batch_plan(fft_batch_t *out, int n, const fft_item_desc *items, int prec
     // separate stages need no more LDS either way
     b->tw_lds = b->any_fused && tw_fits;
     b->lds = (std::max(lds, b->tw_lds ? lds_tw : (size_t)0) + 15) & ~(size_t)15;
-    // Every FFT step of a batch runs radices 2, 3, 4 and 5 only (8 and 16
-    // become 4 x 2 and 4 x 4, in place), in the fused and the separate
-    // schedules alike so that the two stay bit-identical.  When every stage is
-    // a fused unit (no LEAVE_PERMUTED, no BATCH_NO_FUSE) the batch then runs
-    // batch_kernel's LEAN form: without the separate stage kernels and the
-    // larger passes it holds four waves per SIMD instead of three (config 5:
-    // 5.95 -> 5.33 ms).
+    // Every FFT step of a batch runs radices 2 to 6 and 8 only (16 becomes
+    // 4 x 4, in place), in the fused and the separate schedules alike so that
+    // the two stay bit-identical.  When every stage is a fused unit (no
+    // LEAVE_PERMUTED, no BATCH_NO_FUSE) the batch then runs batch_kernel's
+    // LEAN form: without the separate stage kernels and the larger passes it
+    // holds four waves per SIMD instead of three (256 uneven items 5.95 -> 5.33 ms when
+    // the two forms differed in that alone).
     b->lean = !(flags & (FFTRW_FLAG_LEAVE_PERMUTED | FFTRW_FLAG_BATCH_NO_FUSE));
     for (fft_plan_t p : b->plans)
         if (p->T * (int64_t)sizeof(float2) >= (int64_t{1} << 32)) b->lean = false;  // 32-bit offsets
@@ -605,10 +640,15 @@ int fft_batch_plan(fft_batch_t *out, int n, const fft_item_desc *items, int prec
             FftDesc &f = d.fft[t];
             int rad[kMaxPasses], np = 0;
             bool fits = true;
+            int def[kMaxPasses];
+            if (f.npass == factor_radices(f.N, def) && std::equal(def, def + f.npass, f.radix)) {
+                f.npass = batch_radices(f.N, f.radix);
+                continue;
+            }
             for (int q = 0; q < f.npass && fits; ++q) {
                 const int r = f.radix[q];
-                const int nparts = (r == 8 || r == 16) ? 2 : 1;
-                const int parts[2] = {nparts == 2 ? 4 : r, r == 16 ? 4 : 2};
+                const int nparts = r == 16 ? 2 : 1;
+                const int parts[2] = {nparts == 2 ? 4 : r, 4};
                 if (np + nparts > kMaxPasses) {
                     fits = false;
                     break;
@@ -679,7 +719,7 @@ int fft_batch_plan(fft_batch_t *out, int n, const fft_item_desc *items, int prec
     for (int64_t u : b->level_units) units += u;
     log_line(1, "batch of %d items: %lld units in %zu stage levels, %d resident groups, %s stages%s%s", n,
              (long long)units, b->level_units.size(), b->grid, b->any_fused ? "fused" : "separate",
-             b->lean ? " (lean kernel: fused units of radices 2..5)" : "", tuned ? ", tuned" : "");
+             b->lean ? " (lean kernel: fused units of radices 2 to 6 and 8)" : "", tuned ? ", tuned" : "");
     *out = b;
     return FFTRW_OK;
 }

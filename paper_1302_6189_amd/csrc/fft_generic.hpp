@@ -147,10 +147,13 @@ __device__ __forceinline__ void store_block(C *__restrict__ dst, const C *lds, i
 
 // One work-group's share of a batched row FFT: rows [blk * RW, blk * RW + RW).
 // TW_LDS: the N-entry twiddle table is staged in LDS after the rows (the
-// caller sized the block for it), so the passes read it there.  LEAN: the
-// radices are 2, 3, 4 and 5 only (the caller checked), so the passes of 8 and
-// 16 are not compiled in and the kernel holds fewer registers.
-template <typename C, int DIR, bool TW_LDS = false, bool LEAN = false>
+// caller sized the block for it), so the passes read it there.  RADICES: the
+// radices above 5 that the caller's steps may have (bit r: radix r); a kernel
+// without the large ones holds fewer registers.
+constexpr unsigned kRadSmall = 0;
+constexpr unsigned kRadRows = 1u << 8 | 1u << 16;
+constexpr unsigned kRadBatch = 1u << 6 | 1u << 8;
+template <typename C, int DIR, bool TW_LDS = false, unsigned RADICES = kRadRows>
 __device__ __forceinline__ void fft_rows_block(const C *in, C *out, const FftDesc &d, int64_t blk,
                                                typename RealOf<C>::type scale, bool do_scale, C *lds)
 {
@@ -182,11 +185,14 @@ __device__ __forceinline__ void fft_rows_block(const C *in, C *out, const FftDes
         case 3: stockham_pass<3, DIR>(lrow, N, Ns, lanes, lane, tw, wave); break;
         case 4: stockham_pass<4, DIR>(lrow, N, Ns, lanes, lane, tw, wave); break;
         case 5: stockham_pass<5, DIR>(lrow, N, Ns, lanes, lane, tw, wave); break;
+        case 6:
+            if constexpr (RADICES >> 6 & 1) stockham_pass<6, DIR>(lrow, N, Ns, lanes, lane, tw, wave);
+            break;
         case 8:
-            if constexpr (!LEAN) stockham_pass<8, DIR>(lrow, N, Ns, lanes, lane, tw, wave);
+            if constexpr (RADICES >> 8 & 1) stockham_pass<8, DIR>(lrow, N, Ns, lanes, lane, tw, wave);
             break;
         case 16:
-            if constexpr (!LEAN) stockham_pass<16, DIR>(lrow, N, Ns, lanes, lane, tw, wave);
+            if constexpr (RADICES >> 16 & 1) stockham_pass<16, DIR>(lrow, N, Ns, lanes, lane, tw, wave);
             break;
         default: break;
         }

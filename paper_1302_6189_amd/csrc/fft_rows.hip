@@ -37,7 +37,7 @@ __global__ void __launch_bounds__(kThreads)
     fft_rows_kernel(const C *in, C *out, FftDesc d, typename RealOf<C>::type scale, int do_scale)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    fft_rows_block<C, DIR, TW_LDS, LEAN>(in, out, d, blockIdx.x, scale, do_scale != 0, reinterpret_cast<C *>(smem_raw));
+    fft_rows_block<C, DIR, TW_LDS, LEAN ? kRadSmall : kRadRows>(in, out, d, blockIdx.x, scale, do_scale != 0, reinterpret_cast<C *>(smem_raw));
 }
 
 // Radix lists without 8 and 16 (lengths with at most two factors 2, or the
@@ -95,7 +95,7 @@ __global__ void __launch_bounds__(kThreads)
                              typename RealOf<C>::type scale, int do_scale)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    fft_xpose_unit<C, DIR, TW_LDS, LEAN>(in, out, f, d, rw, G, blockIdx.x, scale, do_scale != 0, smem_raw);
+    fft_xpose_unit<C, DIR, TW_LDS, LEAN ? kRadSmall : kRadRows>(in, out, f, d, rw, G, blockIdx.x, scale, do_scale != 0, smem_raw);
 }
 
 // one FFT step of 2,3,5-smooth rows fused with the transpose that follows

@@ -232,8 +232,8 @@ struct NoHook {
 
 // Unit `unit` of a fused step: v-block unit % tiles_v of G consecutive slices.
 // TW_LDS: the twiddle table is staged in LDS (the caller checked unit_tw_fits
-// and sized the LDS block with it).  LEAN: the step's radices are 2, 3, 4 and
-// 5 only (the caller made sure), so the larger passes are not compiled in.
+// and sized the LDS block with it).  RADICES: the radices above 5 compiled in,
+// as in fft_rows_block.
 // OFF32: `in` and `out` each hold fewer than 2^32 bytes (the caller made
 // sure), and HBM addresses are formed from 32-bit offsets.  CACHED (the
 // batch): cached loads, and streaming stores only of whole 128-byte lines.
@@ -247,7 +247,7 @@ struct NoHook {
 // when the level's end writes it back).  hook() runs once the unit's rows are in LDS, after a barrier that every
 // thread passed after entering the unit; no HBM access of the unit's is in
 // flight then except the owner-count atomics.
-template <typename C, int DIR, bool TW_LDS, bool LEAN = false, bool OFF32 = false, bool CACHED = false,
+template <typename C, int DIR, bool TW_LDS, unsigned RADICES = kRadRows, bool OFF32 = false, bool CACHED = false,
           typename Hook = NoHook>
 __device__ __forceinline__ void fft_xpose_unit(const C *__restrict__ in, C *__restrict__ out, const FftDesc &f,
                                                const XposeDesc &d, int rw, int G, int64_t unit,
@@ -326,11 +326,14 @@ __device__ __forceinline__ void fft_xpose_unit(const C *__restrict__ in, C *__re
         case 3: stockham_pass<3, DIR>(lrow, N, Ns, lanes, lane, tw, wave); break;
         case 4: stockham_pass<4, DIR>(lrow, N, Ns, lanes, lane, tw, wave); break;
         case 5: stockham_pass<5, DIR>(lrow, N, Ns, lanes, lane, tw, wave); break;
+        case 6:
+            if constexpr (RADICES >> 6 & 1) stockham_pass<6, DIR>(lrow, N, Ns, lanes, lane, tw, wave);
+            break;
         case 8:
-            if constexpr (!LEAN) stockham_pass<8, DIR>(lrow, N, Ns, lanes, lane, tw, wave);
+            if constexpr (RADICES >> 8 & 1) stockham_pass<8, DIR>(lrow, N, Ns, lanes, lane, tw, wave);
             break;
         case 16:
-            if constexpr (!LEAN) stockham_pass<16, DIR>(lrow, N, Ns, lanes, lane, tw, wave);
+            if constexpr (RADICES >> 16 & 1) stockham_pass<16, DIR>(lrow, N, Ns, lanes, lane, tw, wave);
             break;
         default: break;
         }
