@@ -240,6 +240,10 @@ template <int DIR, typename C> struct Dft<3, DIR, C> {
     }
 };
 
+// The sines enter each output on their own: sin(2 pi/5) (b1 + q b2) with the
+// ratio q of the two sines has two operations less, but both roundings in
+// every output, and complex64 rows of 625 and 3125 points then err by 1.33
+// and 1.51e-7 instead of 1.21 and 1.35e-7 (against 80 bits).
 template <int DIR, typename C> struct Dft<5, DIR, C> {
     static __device__ __forceinline__ void run(C *x)
     {
@@ -247,19 +251,17 @@ template <int DIR, typename C> struct Dft<5, DIR, C> {
         const Real c1 = (Real)0.30901699437494742410229341718282;   // cos(2 pi/5)
         const Real c2 = (Real)-0.80901699437494742410229341718282;  // cos(4 pi/5)
         const Real s1 = (Real)0.95105651629515357211643933337938;   // sin(2 pi/5)
-        const Real q = (Real)0.61803398874989484820458683436564;    // sin(4 pi/5) / sin(2 pi/5)
+        const Real s2 = (Real)0.58778525229247312916870595463907;   // sin(4 pi/5)
         C a1 = cadd(x[1], x[4]), a2 = cadd(x[2], x[3]);
         C b1 = rot90<DIR>(csub(x[1], x[4])), b2 = rot90<DIR>(csub(x[2], x[3]));
         C y0 = cadd(x[0], cadd(a1, a2));
         C m1 = cfma(c2, a2, cfma(c1, a1, x[0]));
         C m2 = cfma(c1, a2, cfma(c2, a1, x[0]));
-        C n1 = cfma(q, b2, b1);
-        C n2 = cfma(q, b1, mk<C>(-b2.x, -b2.y));
         x[0] = y0;
-        x[1] = cfma(s1, n1, m1);
-        x[4] = cfma(-s1, n1, m1);
-        x[2] = cfma(s1, n2, m2);
-        x[3] = cfma(-s1, n2, m2);
+        x[1] = cfma(s1, b1, cfma(s2, b2, m1));
+        x[4] = cfma(-s1, b1, cfma(-s2, b2, m1));
+        x[2] = cfma(-s1, b2, cfma(s2, b1, m2));
+        x[3] = cfma(s1, b2, cfma(-s2, b1, m2));
     }
 };
 
