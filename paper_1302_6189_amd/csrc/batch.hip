@@ -516,8 +516,7 @@ int fft_batch_plan(fft_batch_t *out, int n, const fft_item_desc *items, int prec
         d.buf[2] = (float2 *)p->work;
         d.inv_scale = (float)(1.0 / (double)p->T);
         int64_t units = 0;
-        // fused schedule: one unit = RW rows consecutive in v of one slice, the
-        // largest power of two with RW (N + padding) <= 4096 that the v axis can fill
+        // fused schedule: a unit's shape is fused_unit_shape's
         d.fused = !(flags & FFTRW_FLAG_BATCH_NO_FUSE);
         if (d.fused) {
             d.nstage = it.M;
@@ -630,7 +629,7 @@ int fft_batch_plan(fft_batch_t *out, int n, const fft_item_desc *items, int prec
     // LEAVE_PERMUTED, no BATCH_NO_FUSE) the batch then runs batch_kernel's
     // LEAN form: without the separate stage kernels and the larger passes it
     // holds four waves per SIMD instead of three (256 uneven items 5.95 -> 5.33 ms when
-    // the two forms differed in that alone).
+    // it was introduced).
     b->lean = !(flags & (FFTRW_FLAG_LEAVE_PERMUTED | FFTRW_FLAG_BATCH_NO_FUSE));
     for (fft_plan_t p : b->plans)
         if (p->T * (int64_t)sizeof(float2) >= (int64_t{1} << 32)) b->lean = false;  // 32-bit offsets

@@ -182,7 +182,7 @@ int make_fft_desc(fft_plan_impl *pl, int t, FftDesc *d, bool generic_rows, const
 int dev_alloc(fft_plan_impl *pl, void **p, size_t bytes);
 
 // The twiddle table a descriptor's kernel reads: the per-pass table of the
-// compile-time power-of-two kernel, else w_N^e for e < N, generated on the
+// compile-time row kernels, else w_N^e for e < N, generated on the
 // device in FP64 and rounded.
 int make_desc_twiddles(fft_plan_impl *pl, const FftDesc &d, void **tw)
 {
