@@ -545,7 +545,8 @@ int plan_create(fft_plan_t *plan, int M, const int64_t *dims, int64_t P, const i
     // analytic amounts (and relabellings for the matched reading).  A plan on
     // an arena lives for one exec whose caller cannot ask for its amounts, and
     // its ownership is literal: with their O(P) count a 64^3 call kept the host
-    // 21.2 us at N_p = 16 and 26.1 at 64, without it 18.1 at either
+    // 19.7 us at N_p = 16 and 24.6 at 64, without it 18.0 and 17.8 (processes in
+    // which a plan's exec takes 10.1 us; in others every call takes 1 us more)
     pl->analytic.assign(M, 0);
     pl->mu.assign(M, {});
     for (int t = 0; t < M && !arena; ++t) {
