@@ -30,6 +30,7 @@ hipError_t ct_make_twiddles(int N, bool fp64, void *tw, hipStream_t s);
 bool ct_plan_step(int N, bool fp64, const XposeDesc &d, CtStep *step);
 hipError_t launch_ct_fused(const CtStep &step, const void *tw, const XposeDesc &d, int dir, const void *in, void *out,
                            double scale, CachePolicy policy, hipStream_t s);
+int count_beside(const XposeDesc &d, int threads);
 hipError_t launch_count(const XposeDesc &d, hipStream_t s);
 hipError_t launch_ct_rows(int N, bool fp64, const void *tw, int64_t nrows, int dir, const void *in, void *out,
                           double scale, CachePolicy policy, hipStream_t s);
@@ -391,7 +392,14 @@ int run_fused_step(fft_plan_impl *pl, int t, int nx, int dir, const void *src, v
 {
     const double scale = (dir > 0 && t == pl->M - 1) ? 1.0 / (double)pl->T : 1.0;
     const FftDesc &d = pl->fft[t];
-    const XposeDesc &x = pl->xp[t];
+    // counted by groups of the step's own launch, or in a launch apart: many
+    // pieces of split rows, and rows of single points, whose unit adds to a
+    // counter that nothing resets here
+    XposeDesc x = pl->xp[t];
+    if (x.count) {
+        x.count = pl->fuse_kind[t] == 2 ? 0 : count_beside(x, pl->fuse_kind[t] == 1 ? pl->ct_step[t].threads : kThreads);
+        if (!x.count) HIP_TRY(launch_count(pl->xp[t], s), "owner count launch");
+    }
     if (pl->fuse_kind[t] == 1) {
         HIP_TRY(launch_ct_fused(pl->ct_step[t], d.tw, x, dir, src, dst, scale,
                                 cache_policy(pl, t == nx - 1, pl->ct_step[t].whole), s),
@@ -401,12 +409,8 @@ int run_fused_step(fft_plan_impl *pl, int t, int nx, int dir, const void *src, v
                                       cache_policy(pl, t == nx - 1, x.Nv % 16 == 0).nt_store, s),
                 "fused mfma fft+transpose launch");
     } else {
-        // single points: the run-time-radix unit, its count apart (the unit
-        // adds to its counter, which nothing resets here)
-        XposeDesc y = x;
-        y.count = 0;
-        HIP_TRY(launch_fft_xpose_generic(d, y, pl->esz == 16, dir, src, dst, scale, s), "fused fft+transpose launch");
-        if (x.count) HIP_TRY(launch_count(x, s), "owner count launch");
+        // single points: the run-time-radix unit
+        HIP_TRY(launch_fft_xpose_generic(d, x, pl->esz == 16, dir, src, dst, scale, s), "fused fft+transpose launch");
     }
     return FFTRW_OK;
 }

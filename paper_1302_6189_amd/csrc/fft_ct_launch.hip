@@ -199,16 +199,48 @@ hipError_t ct_make_twiddles(int N, bool fp64, void *tw, hipStream_t s)
     return hipGetLastError();
 }
 
-// a transpose's owner changes alone
-__global__ void __launch_bounds__(kThreads) count_kernel(const XposeDesc d)
+// The form (XposeDesc::count) in which groups of `threads` beside a step's own
+// count its transpose, 0 if that needs a launch apart.  Split rows (A's owner
+// changes along u or B's along v) are counted beside the step while every
+// thread of the groups has one piece at most, which the step hides (128^3 at
+// 16,385 processes 26 us, 64 apart); more pieces fill the chip by themselves
+// (256^3, one process per point: 856 us apart, 23 ms on groups for whole rows).
+int count_beside(const XposeDesc &d, int threads)
 {
-    __shared__ unsigned long long part[kThreads / 64];
+    bool split = false;
+    for (int j = 0; j < d.ka; ++j) split = split || d.srca[j] == 4;
+    for (int j = 0; j < d.kb; ++j) split = split || d.srcb[j] == 3;
+    if (!split) return 1;
+    const int64_t rows = d.nslices * d.Nv, pieces = count_pieces(d);
+    if (rows > (int64_t)kCountBlock * threads / pieces) return 0;
+    int lg = 0;
+    while ((2 << lg) < pieces) ++lg;
+    return 2 + lg;
+}
+
+// a transpose's owner changes alone: one word of the counter per group, so
+// large groups where rows are split
+constexpr int kCountThreads = 1024;
+__global__ void __launch_bounds__(kCountThreads) count_kernel(const XposeDesc d)
+{
+    __shared__ unsigned long long part[kCountThreads / 64];
     count_share(d, blockIdx.x, gridDim.x, part);
 }
 
 hipError_t launch_count(const XposeDesc &d, hipStream_t s)
 {
-    hipLaunchKernelGGL(count_kernel, dim3(count_groups(d, kThreads)), dim3(kThreads), 0, s, d);
+    XposeDesc x = d;
+    int threads = kThreads;
+    x.count = count_beside(d, threads);
+    if (!x.count) {
+        // two items for every thread the chip holds, or a piece per item
+        threads = kCountThreads;
+        const int64_t items = 2 * (int64_t)kCountBlock * threads, pieces = count_pieces(d);
+        int lg = 0;
+        while (((d.nslices * d.Nv) << lg) < items && (2 << lg) < pieces) ++lg;
+        x.count = 2 + lg;
+    }
+    hipLaunchKernelGGL(count_kernel, dim3(count_groups(x, threads)), dim3(threads), 0, s, x);
     return hipGetLastError();
 }
 

@@ -52,7 +52,8 @@ struct XposeDesc {
     // tiling
     int TU, TV, G;    // tile extents along u, v and number of batch slices per tile
     int64_t tiles_u, tiles_v, tiles_g;
-    // owner counting (0 = off)
+    // owner counting: 0 off, 1 on; groups that count a whole transpose of split
+    // rows: 2 + log2 of the parts of a row (see count_share)
     int count;
     int ka, kb;              // levels of A and B
     int srca[5], srcb[5];    // for each leading axis: 0..2 batch index, 3 = v, 4 = u

@@ -166,18 +166,14 @@ __device__ __forceinline__ int64_t row_keep(const XposeDesc &d, const SliceRows 
     return keep;
 }
 
-// Points of the rows v in [v0, v1) of a batch slice that keep their owner.
-// Below level M A's owner is constant along u and B's along v, so the rows
+// Points of the rows v in [v0, v1) of a batch slice that keep their owner,
+// below level M: A's owner is constant along u and B's along v, so the rows
 // come in pieces of constant A owner whose intervals of u are the same.
 __device__ __forceinline__ int64_t rows_keep(const XposeDesc &d, const int *c, int64_t v0, int64_t v1)
 {
     const bool narrow = d.owner32 != 0;
     const SliceRows r = slice_rows(d, c);
     int64_t keep = 0;
-    if (r.wau != 0 || r.wbv != 0) {
-        for (int64_t v = v0; v < v1; ++v) keep += row_keep(d, r, v, 0, d.Nu);
-        return keep;
-    }
     for (int64_t v = v0; v < v1;) {
         const int64_t oa = owner_of_row(r.ra0 + v * r.wav, d.P, d.Ra, narrow);
         int64_t next = v1;
@@ -205,40 +201,65 @@ __device__ __forceinline__ int tile_moved(const XposeDesc &d, int64_t g0, int ng
     return moved;
 }
 
-// Owner changes of a whole transpose, counted by `groups` work-groups: items of
-// slices, or parts of slices when there are few.  The count depends on the
-// decompositions alone: on groups of their own it costs the transform nothing
-// (512^3: 1.2% when the row groups counted in front of their first barrier),
-// and short kernels no reset launch (32^3 complex128 18.9 -> 13.8 us), as
-// every word of the counter is written.
+// Owner changes of a whole transpose, counted by `groups` work-groups.  The
+// count depends on the decompositions alone: on groups of their own it costs
+// the transform nothing (512^3: 1.2% when the row groups counted in front of
+// their first barrier), and short kernels no reset launch (32^3 complex128
+// 18.9 -> 13.8 us), as every word of the counter is written.
+//
+// Whole rows: the items are slices, or parts of slices when there are few.
 __host__ __device__ inline uint32_t count_chunks(const XposeDesc &d)
 {
     const uint32_t n = d.nslices < 8192 ? 8192u / (uint32_t)d.nslices : 1u;
     return n < (uint32_t)d.Nv ? n : (uint32_t)d.Nv;
 }
-// two items a thread
+// Split rows (level M): an item is one row's share of 2^lg parts along u, lg
+// being count - 2.  A row comes in about count_pieces pieces of constant A
+// owner, of seven 64-bit divisions each.
+inline int64_t count_pieces(const XposeDesc &d)
+{
+    for (int j = 0; j < d.ka; ++j)
+        if (d.srca[j] == 4) return (int64_t)((__int128)d.P * d.Nu / d.Ra) + 1;
+    return 1;
+}
+// whole rows: two items a thread; split rows: one
 inline int count_groups(const XposeDesc &d, int threads)
 {
-    const int64_t n = d.nslices * count_chunks(d) / (2 * threads);
+    const int64_t n = d.count >= 2 ? ((d.nslices * d.Nv) << (d.count - 2)) / threads
+                                   : d.nslices * count_chunks(d) / (2 * threads);
     return (int)(n < 16 ? 16 : n > kCountBlock ? kCountBlock : (n + 7) / 8 * 8);
 }
 
 // The share of group `group`; `part` holds one word per wave.
 __device__ __forceinline__ void count_share(const XposeDesc &d, int group, int groups, unsigned long long *part)
 {
-    const uint32_t Nv = (uint32_t)d.Nv, ns = (uint32_t)d.nslices, chunks = count_chunks(d);
-    const uint32_t per = (Nv + chunks - 1) / chunks;
+    const uint64_t first = (uint64_t)group * blockDim.x + threadIdx.x, step = (uint64_t)groups * blockDim.x;
     unsigned long long moved = 0;
-    for (uint64_t i = (uint64_t)group * blockDim.x + threadIdx.x; i < (uint64_t)ns * chunks;
-         i += (uint64_t)groups * blockDim.x) {
-        // (chunks > 1 only below 8192 slices: 32 bits hold the product)
-        const uint32_t g = chunks == 1 ? (uint32_t)i : (uint32_t)i / chunks;
-        const uint32_t v0 = ((uint32_t)i - g * chunks) * per, v1 = min(Nv, v0 + per);
-        if (v0 >= v1) continue;
-        int c[3];
-        int64_t ab, bb;
-        slice_coords(d, g, c, &ab, &bb);
-        moved += (unsigned long long)((int64_t)(v1 - v0) * d.Nu - rows_keep(d, c, v0, v1));
+    int c[3];
+    int64_t ab, bb;
+    if (d.count >= 2) {
+        const int lg = d.count - 2;
+        const uint64_t rows = (uint64_t)(d.nslices * d.Nv);
+        const int64_t len = (d.Nu + (1 << lg) - 1) >> lg;
+        for (uint64_t i = first; i < rows << lg; i += step) {
+            const uint64_t row = i >> lg;
+            const int64_t u0 = (int64_t)(i & ((1u << lg) - 1)) * len, nu = min<int64_t>(len, d.Nu - u0);
+            if (nu <= 0) continue;
+            const uint64_t g = rows >> 32 ? row / (uint32_t)d.Nv : (uint32_t)row / (uint32_t)d.Nv;
+            slice_coords(d, (int64_t)g, c, &ab, &bb);
+            moved += (unsigned long long)(nu - row_keep(d, slice_rows(d, c), (int64_t)(row - g * d.Nv), u0, nu));
+        }
+    } else {
+        const uint32_t Nv = (uint32_t)d.Nv, ns = (uint32_t)d.nslices, chunks = count_chunks(d);
+        const uint32_t per = (Nv + chunks - 1) / chunks;
+        for (uint64_t i = first; i < (uint64_t)ns * chunks; i += step) {
+            // (chunks > 1 only below 8192 slices: 32 bits hold the product)
+            const uint32_t g = chunks == 1 ? (uint32_t)i : (uint32_t)i / chunks;
+            const uint32_t v0 = ((uint32_t)i - g * chunks) * per, v1 = min(Nv, v0 + per);
+            if (v0 >= v1) continue;
+            slice_coords(d, g, c, &ab, &bb);
+            moved += (unsigned long long)((int64_t)(v1 - v0) * d.Nu - rows_keep(d, c, v0, v1));
+        }
     }
     for (int off = 32; off > 0; off >>= 1) moved += __shfl_xor(moved, off);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = moved;
