@@ -132,15 +132,16 @@ __device__ __forceinline__ float2 *batch_buf(const BatchItemDev &it, int kind)
     return it.buf[__builtin_amdgcn_readfirstlane(kind)];
 }
 
-// The inverse (whose last stage also scales) is held to three waves per SIMD
-// (at most 168 VGPRs; it needs one more otherwise, which would leave two).
-// The forward fits without the hint and runs 1% faster without it.
+// Without LEAN the kernel is held to three waves per SIMD (at most 168 VGPRs;
+// the stage kernels need a few more otherwise, which would leave two: 256
+// uneven items 3.23 -> 4.10 ms with LEAVE_PERMUTED, 5.70 -> 6.79 with
+// BATCH_NO_FUSE, with radix 16 compiled in as well, which no step has).
 // LEAN: every stage of every item is a fused unit with radices 2 to 6 and 8
 // only, and every item's buffers hold fewer than 2^32 bytes (32-bit offsets);
 // without the other stage kernels and the larger passes the kernel fits four
 // waves per SIMD.
 template <int DIR, bool TW_LDS, bool LEAN>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(LEAN ? 4 : (DIR > 0 ? 3 : 1))))
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(LEAN ? 4 : 3)))
     batch_kernel(const BatchItemDev *__restrict__ items, const BatchTask *__restrict__ tasks,
                  const int *__restrict__ level_task0, const int64_t *__restrict__ level_units, int nlevels,
                  BatchLevelCtr *ctr, unsigned long long *timeouts, unsigned long long wait_ticks)
@@ -251,9 +252,9 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(L
             }
             if (it.fused && st < it.nx) {
                 const bool last = st == it.M - 1;
-                fft_xpose_unit<float2, DIR, TW_LDS, kRadBatch | kRadRows, false, true>(src, dst, it.fft[st], it.xp[st], it.frw[st], it.fg[st], local,
-                                                    DIR > 0 && last ? it.inv_scale : 1.f, DIR > 0 && last, smem,
-                                                    publish);
+                fft_xpose_unit<float2, DIR, TW_LDS, kRadBatch, false, true>(
+                    src, dst, it.fft[st], it.xp[st], it.frw[st], it.fg[st], local,
+                    DIR > 0 && last ? it.inv_scale : 1.f, DIR > 0 && last, smem, publish);
                 continue;
             }
             // the other unit kinds take the next unit before they start
@@ -261,14 +262,14 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(L
             publish();
             if (it.fused) {
                 const bool last = st == it.M - 1;
-                fft_rows_block<float2, DIR, false, kRadBatch | kRadRows>(src, dst, it.fft[st], local, DIR > 0 && last ? it.inv_scale : 1.f,
+                fft_rows_block<float2, DIR, false, kRadBatch>(src, dst, it.fft[st], local, DIR > 0 && last ? it.inv_scale : 1.f,
                                             DIR > 0 && last, reinterpret_cast<float2 *>(smem));
                 continue;
             }
             const int t = st >> 1;
             if ((st & 1) == 0) {
                 const bool last = t == it.M - 1;
-                fft_rows_block<float2, DIR, false, kRadBatch | kRadRows>(src, dst, it.fft[t], local, DIR > 0 && last ? it.inv_scale : 1.f,
+                fft_rows_block<float2, DIR, false, kRadBatch>(src, dst, it.fft[t], local, DIR > 0 && last ? it.inv_scale : 1.f,
                                             DIR > 0 && last, reinterpret_cast<float2 *>(smem));
             } else {
                 switch (it.xv[t]) {
@@ -638,25 +639,19 @@ int fft_batch_plan(fft_batch_t *out, int n, const fft_item_desc *items, int prec
         for (int t = 0; t < d.M; ++t) {
             FftDesc &f = d.fft[t];
             int rad[kMaxPasses], np = 0;
-            bool fits = true;
             int def[kMaxPasses];
             if (f.npass == factor_radices(f.N, def) && std::equal(def, def + f.npass, f.radix)) {
                 f.npass = batch_radices(f.N, f.radix);
                 continue;
             }
-            for (int q = 0; q < f.npass && fits; ++q) {
-                const int r = f.radix[q];
-                const int nparts = r == 16 ? 2 : 1;
-                const int parts[2] = {nparts == 2 ? 4 : r, 4};
-                if (np + nparts > kMaxPasses) {
-                    fits = false;
-                    break;
+            // (rows hold at most 4096 = 2^kMaxPasses points, so any list fits)
+            for (int q = 0; q < f.npass; ++q) {
+                if (f.radix[q] == 16) {
+                    rad[np++] = 4;
+                    rad[np++] = 4;
+                } else {
+                    rad[np++] = f.radix[q];
                 }
-                for (int k = 0; k < nparts; ++k) rad[np++] = parts[k];
-            }
-            if (!fits) {
-                b->lean = false;  // keeps the step's own radices
-                continue;
             }
             f.npass = np;
             for (int q = 0; q < np; ++q) f.radix[q] = rad[q];
