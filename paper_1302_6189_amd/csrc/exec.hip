@@ -329,6 +329,17 @@ CachePolicy cache_policy(const fft_plan_impl *pl, bool last, bool whole_lines)
             whole_lines && (bytes >= (size_t)1000000000 || bytes <= ((size_t)20 << 20) || last)};
 }
 
+// ... of rows alone, in a plan of separate kernels or a step by itself.  Stores
+// stream.  So do loads, but of the smallest arrays and of those from the L2s'
+// size to the Infinity Cache's.  Forward transforms in separate kernels,
+// streaming / cached loads: 64x64x512 (17 MB) 44 / 56 us, 128^3 (17 MB) 44 / 46,
+// 4096x1024 (34 MB) 58 / 53, 256^3 (134 MB) 287 / 250, 405^3 (531 MB) 1394 / 1524.
+CachePolicy rows_policy(const fft_plan_impl *pl)
+{
+    const size_t bytes = (size_t)pl->T * pl->esz;
+    return {bytes > ((size_t)256 << 20) || (bytes > ((size_t)4 << 20) && bytes <= ((size_t)24 << 20)), true};
+}
+
 int run_fft_desc(fft_plan_impl *pl, const FftDesc &d, int dir, const void *in, void *out, double scale,
                  hipStream_t s)
 {
@@ -337,7 +348,7 @@ int run_fft_desc(fft_plan_impl *pl, const FftDesc &d, int dir, const void *in, v
         return FFTRW_OK;
     }
     if (d.ct) {
-        HIP_TRY(launch_ct_rows(d.N, pl->esz == 16, d.tw, d.nrows, dir, in, out, scale, cache_policy(pl, false, true), s),
+        HIP_TRY(launch_ct_rows(d.N, pl->esz == 16, d.tw, d.nrows, dir, in, out, scale, rows_policy(pl), s),
                 "fft pass launch");
         return FFTRW_OK;
     }

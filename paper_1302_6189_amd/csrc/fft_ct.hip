@@ -34,7 +34,9 @@ template <typename C, int N> CtEntry entry()
     e.pitch = ct_row_pitch<P>();
     e.staged = !P::DIRECT;
     e.fused = &ct_fused_kernel<C, N>;
-    e.rows = &ct_rows_kernel<C, N>;
+    e.rows = &ct_rows_kernel<C, P, false>;
+    if constexpr (N * sizeof(C) % 128 != 0) e.rows_block = &ct_rows_kernel<C, P, true>;
+    if constexpr (!P::DIRECT || !P::STORE_DIRECT) e.rows_straight = &ct_rows_kernel<C, CtStraight<C, N>, false>;
     return e;
 }
 

@@ -106,6 +106,27 @@ template <typename C, int N_> struct CtPlan {
     // cover 128 bytes per access, else through LDS
     static constexpr bool DIRECT = L * (int)sizeof(C) * (c.pair ? 2 : 1) >= 128;
     static constexpr bool STORE_DIRECT = L * (int)sizeof(C) >= 128;
+    static constexpr bool LAST_PAIR = false;
+};
+
+// The same lanes and radices with the first and the last pass's butterflies in
+// adjacent pairs per lane, where that leaves no lane idle: rows alone that are
+// read and written straight from and to HBM, 16 bytes per lane.
+template <typename C, int N_> struct CtStraight : CtPlan<C, N_> {
+    using B = CtPlan<C, N_>;
+    static constexpr bool pairs(int R)
+    {
+        return sizeof(C) == 8 && (N_ / R) % 2 == 0 && ct_iters(N_, R, B::L, true) == ct_iters(N_, R, B::L, false);
+    }
+    static constexpr CtChoice paired()
+    {
+        CtChoice p = B::c;
+        p.pair = pairs(p.r[0]);
+        return p;
+    }
+    static constexpr CtChoice c = paired();
+    static constexpr bool LAST_PAIR = pairs(B::c.r[B::NP - 1]);
+    static constexpr bool DIRECT = true, STORE_DIRECT = true;
 };
 
 // compile-time description of pass p of a plan, and of the exchange after it
@@ -113,7 +134,7 @@ template <class P, int p> struct CtPass {
     static constexpr int R = P::c.r[p];
     static constexpr int Ns = CtPass<P, p - 1>::Ns * CtPass<P, p - 1>::R;
     static constexpr int NB = P::N / R;
-    static constexpr bool PAIR = false;
+    static constexpr bool PAIR = p == P::NP - 1 && P::LAST_PAIR;
     static constexpr int IT = ct_iters(P::N, R, P::L, PAIR);
     // (pass 0 has no twiddles)
     static constexpr int tw_off =
@@ -421,6 +442,68 @@ __device__ __forceinline__ void ct_store_staged(C *dst, const C *lds, int nth, i
     }
 }
 
+// Rows alone that are not whole 128-byte lines, between HBM and their LDS
+// buffers as one block, which all threads copy from end to end, so that an
+// access covers whole lines but at the block's ends.
+template <class P, typename C> struct CtBlock {
+    static constexpr int W = sizeof(C) == 8 ? 2 : 1;
+    static constexpr int IT = ct_cdiv(ct_cdiv(P::N, W), P::L);
+    static constexpr int SKIP = ct_row_pitch<P>() - P::N;  // LDS positions between rows
+
+    // f(it, e, l, l2, n): the it-th access of this thread is of the block's
+    // values e .. e + n - 1, which sit at l and (W = 2) l2 in LDS
+    template <typename F> static __device__ __forceinline__ void each(int nth, int nrows, F &&f)
+    {
+        const int total = nrows * P::N;
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const int e = (threadIdx.x + it * nth) * W;
+            if (e >= total) continue;
+            const int row = (uint32_t)e / P::N, l = e + SKIP * row;
+            // (a pair of an odd row's last value and the next row's first)
+            const int l2 = l + 1 + (P::N % 2 != 0 && SKIP != 0 && e + 1 == (row + 1) * P::N ? SKIP : 0);
+            f(it, e, l, l2, P::N % 2 != 0 ? min(W, total - e) : W);
+        }
+    }
+
+    template <bool NT> static __device__ __forceinline__ void load(C *lds, const C *src, int nth, int nrows)
+    {
+        using V = typename CtRaw<C>::type;
+        C val[IT][W];
+        each(nth, nrows, [&](int it, int e, int, int, int n) {
+            if constexpr (W == 2) {
+                if (n == 2) {
+                    const xf4 w = ct_ld<NT>(reinterpret_cast<const xf4 *>(src + e));
+                    val[it][0] = mk<C>(w.x, w.y);
+                    val[it][1] = mk<C>(w.z, w.w);
+                    return;
+                }
+            }
+            const V w = ct_ld<NT>(reinterpret_cast<const V *>(src + e));
+            val[it][0] = mk<C>(w.x, w.y);
+        });
+        each(nth, nrows, [&](int it, int, int l, int l2, int n) {
+            lds[l] = val[it][0];
+            if constexpr (W == 2)
+                if (n == 2) lds[l2] = val[it][1];
+        });
+    }
+
+    template <bool NT> static __device__ __forceinline__ void store(C *dst, const C *lds, int nth, int nrows)
+    {
+        using V = typename CtRaw<C>::type;
+        each(nth, nrows, [&](int, int e, int l, int l2, int n) {
+            if constexpr (W == 2) {
+                if (n == 2) {
+                    ct_st<NT>(xf4{lds[l].x, lds[l].y, lds[l2].x, lds[l2].y}, reinterpret_cast<xf4 *>(dst + e));
+                    return;
+                }
+            }
+            ct_st<NT>(V{lds[l].x, lds[l].y}, reinterpret_cast<V *>(dst + e));
+        });
+    }
+};
+
 // position of column (row of the group) `col` in a frequency's line of the
 // output block: one value of padding per 128 bytes
 template <typename C> __device__ __forceinline__ int ct_col(int col) { return col + (col >> (sizeof(C) == 8 ? 4 : 3)); }
@@ -643,11 +726,15 @@ __global__ void __launch_bounds__((CtPlan<C, N>::MAXNT))
 }
 
 // ---- FFT step alone: rows in place or from `in` to `out` ----------------------
-template <typename C, int N>
-__global__ void __launch_bounds__((CtPlan<C, N>::MAXNT))
-    ct_rows_kernel(const void *in_, void *out_, int64_t nrows, const CtShape s, const void *tw_, double scale)
+// P: CtPlan or CtStraight.  BLOCK: the group's rows go through LDS as one block
+// (CtBlock); otherwise row by row, as the plan says.
+template <typename C, class P, bool BLOCK>
+__global__ void __launch_bounds__(P::MAXNT)
+    ct_rows_kernel(const void *in_, void *out_, int64_t nrows, const void *tw_, double scale, const CtRowsShape s)
 {
-    using P = CtPlan<C, N>;
+    constexpr int N = P::N;
+    using B = CtBlock<P, C>;
+    constexpr bool DIRECT = P::DIRECT && !BLOCK, STORE_DIRECT = P::STORE_DIRECT && !BLOCK;
     extern __shared__ __align__(16) unsigned char smem[];
     C *lds = reinterpret_cast<C *>(smem);
     const int64_t row0 = (int64_t)blockIdx.x << s.lr;
@@ -662,53 +749,83 @@ __global__ void __launch_bounds__((CtPlan<C, N>::MAXNT))
     CtTw<P, 0, C> w0;
     CtTwNext<P, 1, C> w1;
     if constexpr (P::NP > 1) ct_load_tw<P, 1, C>(w1, lane, tw);
-    if constexpr (P::DIRECT) {
+    if constexpr (DIRECT) {
         if (rho < here) {
-            either(s.nt_load, [&](auto nt) { ct_load_direct<P, nt.value, C>(v, in + rho * N, lane); });
+            either(s.flags & kCtNtLoad, [&](auto nt) { ct_load_direct<P, nt.value, C>(v, in + rho * N, lane); });
         } else {
 #pragma unroll
             for (int e = 0; e < CtPass<P, 0>::IT * CtPass<P, 0>::R; ++e) v.x[e] = mk<C>(0, 0);
         }
     } else {
-        either(s.nt_load, [&](auto nt) { ct_load_staged<P, nt.value, C>(lds, in, N, nullptr, nth, here); });
+        either(s.flags & kCtNtLoad, [&](auto nt) {
+            if constexpr (BLOCK)
+                B::template load<nt.value>(lds, in, nth, here);
+            else
+                ct_load_staged<P, nt.value, C>(lds, in, N, nullptr, nth, here);
+        });
         __syncthreads();
         ct_read_row<P, 0, C>(v, row, lane);
         row_sync(P::L <= 64);
     }
-    if (s.inverse) ct_conj<P, 0, C>(v);
+    if (s.flags & kCtInverse) ct_conj<P, 0, C>(v);
     ct_passes<P, 0, C>(v, w0, w1, row, lane, tw, [&](CtVals<P, P::NP - 1, C> &y) {
         using S = CtPass<P, P::NP - 1>;
         using V = typename CtRaw<C>::type;
-        if constexpr (!P::STORE_DIRECT && P::NP > 1) row_sync(P::L <= 64);
-        if (s.inverse) ct_conj<P, P::NP - 1, C>(y);
-        if (s.do_scale) {
+        if constexpr (!STORE_DIRECT && P::NP > 1) row_sync(P::L <= 64);
+        if (s.flags & kCtInverse) ct_conj<P, P::NP - 1, C>(y);
+        if (s.flags & kCtScale) {
             const typename RealOf<C>::type sx = (typename RealOf<C>::type)scale;
 #pragma unroll
             for (int e = 0; e < S::IT * S::R; ++e) y.x[e] = cscale(y.x[e], sx);
         }
+        if constexpr (STORE_DIRECT && S::PAIR) {
 #pragma unroll
-        for (int m = 0; m < S::IT; ++m) {
-            const int j = ct_j<P, P::NP - 1>(lane, m);
-            if (ct_all<P, P::NP - 1>(m) || j < S::NB) {
-                if constexpr (P::STORE_DIRECT) {
-                    if (rho < here) {
-                        V *p = reinterpret_cast<V *>(out + rho * N + j);
-                        either(s.nt_store, [&](auto nt) {
+            for (int m = 0; m < S::IT; m += 2) {
+                const int j = ct_j<P, P::NP - 1>(lane, m);
+                if (rho < here && (ct_all<P, P::NP - 1>(m) || j < S::NB)) {
+                    xf4 *p = reinterpret_cast<xf4 *>(out + rho * N + j);
+                    either(s.flags & kCtNtStore, [&](auto nt) {
 #pragma unroll
-                            for (int i = 0; i < S::R; ++i)
-                                ct_st<nt.value>(V{y.x[m * S::R + i].x, y.x[m * S::R + i].y}, p + i * S::NB);
-                        });
+                        for (int i = 0; i < S::R; ++i) {
+                            C a = y.x[m * S::R + i], b = y.x[(m + 1) * S::R + i];
+                            // (values, not loads of two neighbours of y, which
+                            // would keep y in scratch memory)
+                            asm("" : "+v"(a.x), "+v"(a.y), "+v"(b.x), "+v"(b.y));
+                            ct_st<nt.value>(xf4{a.x, a.y, b.x, b.y}, p + i * (S::NB / 2));
+                        }
+                    });
+                }
+            }
+        } else {
+#pragma unroll
+            for (int m = 0; m < S::IT; ++m) {
+                const int j = ct_j<P, P::NP - 1>(lane, m);
+                if (ct_all<P, P::NP - 1>(m) || j < S::NB) {
+                    if constexpr (STORE_DIRECT) {
+                        if (rho < here) {
+                            V *p = reinterpret_cast<V *>(out + rho * N + j);
+                            either(s.flags & kCtNtStore, [&](auto nt) {
+#pragma unroll
+                                for (int i = 0; i < S::R; ++i)
+                                    ct_st<nt.value>(V{y.x[m * S::R + i].x, y.x[m * S::R + i].y}, p + i * S::NB);
+                            });
+                        }
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < S::R; ++i) row[j + i * S::NB] = y.x[m * S::R + i];
                     }
-                } else {
-#pragma unroll
-                    for (int i = 0; i < S::R; ++i) row[j + i * S::NB] = y.x[m * S::R + i];
                 }
             }
         }
     });
-    if constexpr (!P::STORE_DIRECT) {
+    if constexpr (!STORE_DIRECT) {
         __syncthreads();
-        either(s.nt_store, [&](auto nt) { ct_store_staged<P, nt.value, C>(out, lds, nth, here); });
+        either(s.flags & kCtNtStore, [&](auto nt) {
+            if constexpr (BLOCK)
+                B::template store<nt.value>(out, lds, nth, here);
+            else
+                ct_store_staged<P, nt.value, C>(out, lds, nth, here);
+        });
     }
 }
 

@@ -266,25 +266,48 @@ hipError_t launch_ct_fused(const CtStep &step, const void *tw, const XposeDesc &
     return hipGetLastError();
 }
 
+// Rows alone that pass through LDS in the fused kernels go straight between
+// HBM and registers in a small array, where the way through LDS is latency
+// (64 points, 4 MB 0.81 of the time; 32 MB 0.73 to 1.9 times, by the length).
+constexpr int64_t kStraightBytes = 4 << 20;
+
+// Rows that are not whole lines are copied as one block per group where the
+// array is too large for the Infinity Cache to join the lines' parts (729^3,
+// 3.1 GB: 1583 us row by row, 1226 as blocks), and where rows are short and odd
+// (125 points, 131 MB: 47 and 43 us; longer rows and pairs of values lose:
+// 625 points 39 and 42).
+constexpr int64_t kBlockRowBytes = 1024, kBlockBytes = (int64_t)256 << 20;
+
 hipError_t launch_ct_rows(int N, bool fp64, const void *tw, int64_t nrows, int dir, const void *in, void *out,
                           double scale, CachePolicy policy, hipStream_t s)
 {
     const CtEntry *e = find(N, fp64);
     if (!e) return hipErrorInvalidValue;
     if (nrows <= 0) return hipSuccess;
-    CtShape c{};
+    CtRowsShape c{};
+    // groups of 256 threads, or smaller ones where the chip then holds more
+    // waves (625 points, whose padded rows leave LDS for two groups of 256
+    // threads: 42.7 us for 134 MB, 39.2 in groups of 64) or would have few groups
+    auto resident = [&](int t) {
+        return std::min<int64_t>((int64_t)(kLdsBytes / ((size_t)(t / e->L) * e->pitch * e->esz)) * t, 1024);
+    };
     int threads = std::max(256, e->min_threads);
-    while (threads > e->min_threads && nrows * e->L / threads < 512) threads /= 2;
+    while (threads > e->min_threads &&
+           (resident(threads / 2) > resident(threads) || nrows * e->L / threads < 512))
+        threads /= 2;
     const int rows = threads / e->L;
     while ((1 << c.lr) < rows) ++c.lr;
     const int64_t grid = (nrows + rows - 1) / rows;
     if (grid >= (int64_t)0x7fffffff) return hipErrorInvalidValue;
-    c.nt_load = policy.nt_load;
-    c.nt_store = policy.nt_store;
-    c.inverse = dir > 0;
-    c.do_scale = scale != 1.0;
-    hipLaunchKernelGGL(e->rows, dim3((unsigned)grid), dim3(threads), (size_t)rows * e->pitch * e->esz, s, in, out, nrows,
-                       c, tw, scale);
+    const int64_t row = (int64_t)N * e->esz, bytes = nrows * row;
+    const bool block = e->rows_block && (bytes > kBlockBytes || (N % 2 != 0 && row < kBlockRowBytes));
+    const bool straight = e->rows_straight && bytes <= kStraightBytes;
+    // (parts of lines are left to the caches to join)
+    const bool nt_store = policy.nt_store && (block || straight || row % 128 == 0 || 128 % row == 0);
+    c.flags = (policy.nt_load ? kCtNtLoad : 0) | (nt_store ? kCtNtStore : 0) | (dir > 0 ? kCtInverse : 0) |
+              (scale != 1.0 ? kCtScale : 0);
+    hipLaunchKernelGGL(straight ? e->rows_straight : block ? e->rows_block : e->rows, dim3((unsigned)grid), dim3(threads),
+                       (size_t)rows * e->pitch * e->esz, s, in, out, nrows, tw, scale, c);
     return hipGetLastError();
 }
 

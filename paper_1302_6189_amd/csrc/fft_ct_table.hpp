@@ -63,8 +63,15 @@ struct CtShape {
     CtDiv dtv, db[3];       // divisions by tiles_v and by the batch axes' sizes
 };
 
+// ... of rows alone (few bytes: a small transform waits for its arguments)
+struct CtRowsShape {
+    int lr;             // as above
+    uint32_t flags;     // kCtNtLoad ..
+};
+constexpr uint32_t kCtNtLoad = 1, kCtNtStore = 2, kCtInverse = 4, kCtScale = 8;
+
 using CtFusedKernel = void (*)(const void *, void *, const XposeDesc, const CtShape, const void *, double, int);
-using CtRowsKernel = void (*)(const void *, void *, int64_t, const CtShape, const void *, double);
+using CtRowsKernel = void (*)(const void *, void *, int64_t, const void *, double, const CtRowsShape);
 
 struct CtEntry {
     int N, esz;
@@ -75,6 +82,8 @@ struct CtEntry {
     int staged;  // rows go through LDS first (and need a table of row bases)
     CtFusedKernel fused;
     CtRowsKernel rows;
+    CtRowsKernel rows_block;     // rows that are not whole lines, as one block (else null)
+    CtRowsKernel rows_straight;  // rows otherwise staged in LDS, without (else null)
 };
 
 // a fused step's launch, made once per plan
