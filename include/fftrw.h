@@ -250,9 +250,10 @@ int fft_compare_models(double N, double P, double *out);
  * Fusion: unless flags hold FFTRW_FLAG_SEPARATE or FFTRW_FLAG_STAGED, each
  * FFT step runs fused with the transpose that follows it when every step
  * qualifies (rows of any supported length up to 4096 points for C64, 2048 for
- * C128; in a plan of a split MFMA form, rows of up to 512 points); otherwise
- * the steps and transposes run as separate kernels.  Execs with in == out take one copy
- * more when the number of transposes is odd.  Results are bit-identical
+ * C128; in a plan of a split MFMA form all but 1024, 2048 and 4096 points);
+ * otherwise the steps and transposes run as separate kernels.  Execs with
+ * in == out take one copy more when the number of transposes is odd.  Results
+ * are bit-identical
  * either way; fft_plan_describe's text starts with "fused|" when it fuses.
  * The plan owns its device workspace (fft_workspace_bytes) and twiddle
  * tables; it must outlive every exec enqueued with it.  One exec per plan may

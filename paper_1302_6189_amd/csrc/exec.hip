@@ -712,19 +712,20 @@ int plan_create(fft_plan_t *plan, int M, const int64_t *dims, int64_t P, const i
             }
         }
     }
-    // fusion of every FFT step with its transpose (the default): rows of 2 and
-    // more points use the compile-time kernel of their length, single points
-    // the run-time-radix unit, steps of the split-precision form (256 and 512
-    // points) the MFMA kernel
+    // fusion of every FFT step with its transpose (the default): rows of 2 to
+    // 4096 points (complex128: 2048) use the compile-time kernel of their
+    // length, single points the run-time-radix unit, steps of the
+    // split-precision form (256 and 512 points) the MFMA kernel
     if (!(flags & (FFTRW_FLAG_SEPARATE | FFTRW_FLAG_STAGED)) && !generic_rows) {
         const bool fp64 = pl->esz == 16;
         const int nx = (flags & FFTRW_FLAG_LEAVE_PERMUTED) ? M - 1 : M;
         bool ok = true;
         for (int t = 0; t < nx && ok; ++t) {
             const FftDesc &d = pl->fft[t];
-            // (a plan of the split-precision form fuses with rows of up to 512
-            // points beside the MFMA kernel's)
-            const bool ct_ok = d.ct && !d.mfma && (pl->precision == FFTRW_PREC_NATIVE || d.N <= 512) &&
+            // (a plan of a split form with an axis of 1024, 2048 or 4096 points
+            // has always run separate steps, and says so in fft_plan_describe)
+            const bool ct_ok = d.ct && !d.mfma &&
+                               (pl->precision == FFTRW_PREC_NATIVE || d.N <= 512 || (d.N & (d.N - 1)) != 0) &&
                                ct_plan_step(d.N, fp64, pl->xp[t], &pl->ct_step[t]);
             const bool generic_ok = !d.ct && !d.mfma && d.N + 1 <= (fp64 ? 2048 : 4096);
             pl->fuse_kind[t] = d.mfma ? 3 : (ct_ok ? 1 : (generic_ok ? 2 : 0));
