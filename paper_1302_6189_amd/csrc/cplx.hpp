@@ -329,4 +329,25 @@ template <int DIR, typename C> struct Dft<9, DIR, C> {
     }
 };
 
+// exp(-2 pi i e / n), 0 <= e < n <= 2^28: the angle is reduced to an octant in
+// integers, so that its rounding is a share of an angle of at most pi / 4
+// (-2 e / n rounded as it is puts up to several units of the last place into
+// the roots of every n that is no power of two: complex128 rows of 320 points
+// 2.34e-16 instead of 2.19e-16, of 81 points 2.19e-16 instead of 1.96e-16).
+__device__ inline void unit_root(int e, int n, double *re, double *im)
+{
+    const int o = 8 * e / n, r = 8 * e - o * n;
+    double s, c;
+    sincospi((double)(o % 2 ? n - r : r) / (4.0 * (double)n), &s, &c);
+    double x = o % 2 ? s : c, y = o % 2 ? c : s;
+    const int q = o / 2;  // quarter turns
+    if (q % 2) {
+        const double t = x;
+        x = -y;
+        y = t;
+    }
+    *re = q >= 2 ? -x : x;
+    *im = q >= 2 ? y : -y;
+}
+
 }  // namespace fftrw

@@ -176,7 +176,7 @@ template <typename C> __global__ void __launch_bounds__(kThreads) ct_twiddle_ker
             const int i = (idx - off) / Ns + 1, k = (idx - off) % Ns;
             const int n = Ns * R;
             double s, c;
-            sincospi(-2.0 * (double)((i * k) % n) / (double)n, &s, &c);
+            unit_root((i * k) % n, n, &c, &s);
             out[idx] = mk<C>((typename RealOf<C>::type)c, (typename RealOf<C>::type)s);
         }
         off += cnt;

@@ -17,8 +17,7 @@ __global__ void __launch_bounds__(kThreads) twiddle_kernel(C *out, int64_t n)
     int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= n) return;
     double s, c;
-    // sin/cos of pi * (-2 e / n); the argument is reduced exactly first
-    sincospi(-2.0 * (double)e / (double)n, &s, &c);
+    unit_root((int)e, (int)n, &c, &s);
     out[e] = mk<C>((typename RealOf<C>::type)c, (typename RealOf<C>::type)s);
 }
 
