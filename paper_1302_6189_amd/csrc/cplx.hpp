@@ -127,6 +127,22 @@ template <int DIR, typename C> __device__ __forceinline__ C twmul(C a, C w)
     return DIR < 0 ? cmul(a, w) : cmulc(a, w);
 }
 
+// a * (x + i y) for a constant of a butterfly.  In single precision the constant
+// enters in two parts: its rounding would be in every output that it reaches,
+// in pass after pass (complex64 rows of 2187 points, radix 9, err by 1.36e-7
+// with rounded constants, 1.29e-7 with two parts and 1.32e-7 in radix 3; 4096
+// points, radix 16, by 1.21e-7, 1.17e-7 and, in radix 8, 1.19e-7).
+template <typename C> __device__ __forceinline__ C cmulk(C a, double x, double y)
+{
+    if constexpr (sizeof(C) == 8) {
+        const float hx = (float)x, hy = (float)y, lx = (float)(x - (double)hx), ly = (float)(y - (double)hy);
+        const C e = cmul(a, mk<C>(lx, ly));
+        return mk<C>(fma_(a.x, hx, fma_(-a.y, hy, e.x)), fma_(a.x, hy, fma_(a.y, hx, e.y)));
+    } else {
+        return cmul(a, mk<C>(x, y));
+    }
+}
+
 template <int R, int DIR, typename C> struct Dft;
 
 template <int DIR, typename C> struct Dft<2, DIR, C> {
@@ -181,9 +197,8 @@ template <int DIR, typename C> struct Dft<16, DIR, C> {
     {
         using Real = typename RealOf<C>::type;
         const Real h = (Real)0.70710678118654752440084436210485;
-        const Real c1 = (Real)0.92387953251128675612818318939679;  // cos(pi/8)
-        const Real s1 = (Real)0.38268343236508977172845998403040;  // sin(pi/8)
-        const C w1 = mk<C>(c1, DIR * s1), w3 = mk<C>(s1, DIR * c1), w9 = mk<C>(-c1, -DIR * s1);
+        const double c1 = 0.92387953251128675612818318939679;  // cos(pi/8)
+        const double s1 = 0.38268343236508977172845998403040;  // sin(pi/8)
         C c[4][4];  // c[n][k]: column n (inputs n + 4 i), output k
 #pragma unroll
         for (int n = 0; n < 4; ++n) {
@@ -209,8 +224,8 @@ template <int DIR, typename C> struct Dft<16, DIR, C> {
             x[k + 4] = cadd(b, d);
             x[k + 12] = csub(b, d);
         };
-        odd(c[0][1], cmul(c[1][1], w1), t21, cmul(c[3][1], w3), 1);
-        odd(c[0][3], cmul(c[1][3], w3), t23, cmul(c[3][3], w9), 3);
+        odd(c[0][1], cmulk(c[1][1], c1, DIR * s1), t21, cmulk(c[3][1], s1, DIR * c1), 1);
+        odd(c[0][3], cmulk(c[1][3], s1, DIR * c1), t23, cmulk(c[3][3], -c1, -DIR * s1), 3);
         // row 2: columns 1 and 3 enter times h, column 2 times DIR i
         {
             const C z2 = rot90<DIR>(c[2][2]);
@@ -304,10 +319,6 @@ template <int DIR, typename C> struct Dft<15, DIR, C> : DftCoprime<3, 5, DIR, C>
 template <int DIR, typename C> struct Dft<9, DIR, C> {
     static __device__ __forceinline__ void run(C *x)
     {
-        using Real = typename RealOf<C>::type;
-        const C w1 = mk<C>((Real)0.76604444311897803520239265055542, DIR * (Real)0.64278760968653932632264340990726);
-        const C w2 = mk<C>((Real)0.17364817766693034885171662676931, DIR * (Real)0.98480775301220805936674302458952);
-        const C w4 = mk<C>((Real)-0.93969262078590838405410927732473, DIR * (Real)0.34202014332566873304409961468226);
         C c[3][3];
 #pragma unroll
         for (int n = 0; n < 3; ++n) {
@@ -315,10 +326,11 @@ template <int DIR, typename C> struct Dft<9, DIR, C> {
             for (int i = 0; i < 3; ++i) c[n][i] = x[n + 3 * i];
             Dft<3, DIR, C>::run(c[n]);
         }
-        c[1][1] = cmul(c[1][1], w1);
-        c[1][2] = cmul(c[1][2], w2);
-        c[2][1] = cmul(c[2][1], w2);
-        c[2][2] = cmul(c[2][2], w4);
+        // w9^1, w9^2, w9^2 and w9^4
+        c[1][1] = cmulk(c[1][1], 0.76604444311897803520239265055542, DIR * 0.64278760968653932632264340990726);
+        c[1][2] = cmulk(c[1][2], 0.17364817766693034885171662676931, DIR * 0.98480775301220805936674302458952);
+        c[2][1] = cmulk(c[2][1], 0.17364817766693034885171662676931, DIR * 0.98480775301220805936674302458952);
+        c[2][2] = cmulk(c[2][2], -0.93969262078590838405410927732473, DIR * 0.34202014332566873304409961468226);
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
             C r[3] = {c[0][k], c[1][k], c[2][k]};

@@ -1,6 +1,7 @@
 """Rounding errors of the row kernels against an 80-bit transform, at lengths
-whose twiddles once cost accuracy.  The bounds lie between an emulation of the
-kernels' twiddles with and without the loss."""
+whose twiddles and butterfly constants once cost accuracy.  The bounds lie
+between an emulation of the kernels (complex64: butterflies and twiddles as
+they are) or of their twiddles (complex128) with and without the loss."""
 import numpy as np
 import pytest
 import scipy.fft
@@ -35,8 +36,12 @@ def _smooth(n):
     return n == 1
 
 
-# with rounded angles 2.17e-16 and 2.22e-16, exact 1.94e-16 and about 2.0e-16
-@pytest.mark.parametrize("n,dtype,bound", [(81, np.complex128, 2.06e-16), (320, np.complex128, 2.11e-16)])
+# complex64 with rounded constants 0.963, 1.230, 1.357 and 1.210e-7, in two
+# parts 0.918, 1.168, 1.290 and 1.177e-7; complex128 with rounded angles
+# 2.17e-16 and 2.22e-16, exact 1.94e-16 and about 2.0e-16
+@pytest.mark.parametrize("n,dtype,bound", [(81, np.complex64, 0.945e-7), (729, np.complex64, 1.20e-7),
+                                           (2187, np.complex64, 1.32e-7), (4096, np.complex64, 1.195e-7),
+                                           (81, np.complex128, 2.06e-16), (320, np.complex128, 2.11e-16)])
 def test_rows(gpu_lib, n, dtype, bound):
     err = _error(n, dtype)
     print(n, np.dtype(dtype).name, f"{err:.4e}", flush=True)
