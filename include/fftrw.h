@@ -346,7 +346,8 @@ int fft_plan_set_timing(fft_plan_t plan, int enable);
  * step 2, ..., FFT step M, return transpose (absent with LEAVE_PERMUTED).
  * With FFTRW_FLAG_STAGED each transpose is three stages: pack, exchange,
  * unpack.  When the plan fuses (see fft_plan) each stage is one FFT step
- * together with the transpose that follows it.
+ * together with the transpose that follows it, the last one also with the
+ * copy of an exec in place of an odd number of transposes.
  * ms: host array of capacity `cap`; *n receives the number of stages.
  * Synchronises on the last event.
  */

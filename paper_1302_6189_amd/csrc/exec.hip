@@ -449,15 +449,16 @@ int run_pipeline(fft_plan_impl *pl, const void *in, void *out, hipStream_t s, in
         for (int t = 0; t < nx; ++t) {
             void *dst = fused_dst(pl, nx, t, flip, out);
             if (int rc = run_fused_step(pl, t, nx, dir, src, dst, s)) return rc;
-            if (int rc = mark()) return rc;
             src = dst;
+            if (flip && !leave && t == nx - 1)  // (part of the last stage)
+                HIP_TRY(hipMemcpyAsync(out, src, (size_t)pl->T * pl->esz, hipMemcpyDeviceToDevice, s),
+                        "copy to the output");
+            if (int rc = mark()) return rc;
         }
         if (leave) {
             const double scale = dir > 0 ? 1.0 / (double)pl->T : 1.0;
             if (int rc = run_fft_step(pl, M - 1, dir, src, out, scale, s)) return rc;
             if (int rc = mark()) return rc;
-        } else if (flip) {
-            HIP_TRY(hipMemcpyAsync(out, src, (size_t)pl->T * pl->esz, hipMemcpyDeviceToDevice, s), "copy to the output");
         }
         pl->n_recorded = nev;
         pl->executed = true;
