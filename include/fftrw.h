@@ -450,14 +450,15 @@ int fft_batch_destroy(fft_batch_t batch);
 
 /*
  * fft_autotune -- time candidate kernel parameters for the row lengths and
- * transposes of the given items on the current device and write the winners
- * to the JSON file cache_path: per row length, the radix order and rows per
- * work-group of the generic row kernel; per (u size, v size) transpose, the
- * tile shape, and the radix order of the FFT step fused with it (the built-in
- * order unless another is at least 3% faster); fused batch stages use the
- * latter, separate stages the former.  The cache records the device architecture and library
- * version; fft_batch_plan ignores a cache whose tags do not match.  Uses
- * about 260 MB of device memory while it runs; synchronous.  flags: 0.
+ * transposes of the given items on the current device, in the batched form's
+ * own kernels, and write the winners to the JSON file cache_path: per row
+ * length, the radix order and rows per work-group of the row blocks; per
+ * (u size, v size) transpose, the tile shape, and the radix order of the FFT
+ * step fused with it.  The built-in choice stands unless another is at least
+ * 3% faster.  Fused batch stages use the latter orders, separate stages the
+ * former.  The cache records the device architecture and library version;
+ * fft_batch_plan ignores a cache whose tags do not match.  Uses about 260 MB
+ * of device memory while it runs; synchronous.  flags: 0.
  */
 int fft_autotune(int n, const fft_item_desc *items, const char *cache_path,
                  unsigned flags);

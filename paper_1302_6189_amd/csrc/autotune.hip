@@ -1,22 +1,26 @@
 // autotune.hip -- the autotuner of the batched form.
 //
-// For every row length the given items transform, it times candidate radix
-// orders (partitions of the power-of-two part into radices 16/8/4/2 with at
-// most one pass more than the fewest, each in a few orders, together with the
-// 3s and 5s) and two choices of rows per work-group on the generic row kernel;
-// for every (u size, v size) pair of their transposes it times tile shapes
-// TU x TV (x G slices), and the same radix orders in the FFT step fused with
-// that transpose (the unit the batched form runs by default: its best radix
-// order differs from the separate row kernel's).  Timing uses HIP events on a private stream over a
-// synthetic array of about 16 M complex values.  The winners are written to a
-// small JSON cache tagged with the device architecture and library version;
-// plans built with that cache (fft_batch_plan's tune_cache) use them.
+// Every candidate is timed in the batch's own code (batch.hip: its radices, its
+// cached and streaming accesses, its waves per SIMD) against the batch's
+// built-in choice, which another replaces only if it is 3% faster: near-equal
+// candidates differ by noise on the timing array, and a batch must not become
+// slower by being tuned.  For every row length the given items transform it
+// times radix orders (the fewest passes of 2 to 6 and 8 or one more, each in a
+// few orders) and two choices of rows per work-group in the row blocks; for
+// every (u size, v size) pair of their transposes the tile shapes TU x TV
+// (x G slices), and the radix orders in the FFT step fused with that transpose
+// (the unit the batched form runs by default: its best order differs from the
+// row blocks').  Timing uses HIP events on a private stream over a synthetic
+// array of about 16 M complex values.  The winners are written to a small JSON
+// cache tagged with the device architecture and library version; plans built
+// with that cache (fft_batch_plan's tune_cache) use them.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cstdio>
 #include <cstring>
 #include <fstream>
+#include <functional>
 #include <set>
 #include <sstream>
 #include <string>
@@ -31,12 +35,10 @@
 namespace fftrw {
 
 hipError_t launch_twiddles(void *out, int64_t n, bool fp64, hipStream_t s);
-hipError_t launch_fft_rows(const FftDesc &d, bool fp64, int dir, const void *in, void *out, double scale,
-                           hipStream_t s);
-hipError_t launch_xpose(const XposeDesc &d, size_t esz, const void *in, void *out, hipStream_t s);
-hipError_t launch_fft_xpose_generic(const FftDesc &f, const XposeDesc &d, bool fp64, int dir, const void *in,
-                                    void *out, double scale, hipStream_t s);
-int factor_radices(int64_t n, int *rad);
+hipError_t launch_batch_unit(const FftDesc &f, const XposeDesc &d, const void *in, void *out, hipStream_t s);
+hipError_t launch_batch_rows(const FftDesc &f, const void *in, void *out, hipStream_t s);
+hipError_t launch_batch_tile(const XposeDesc &d, const void *in, void *out, hipStream_t s);
+int batch_radices(int64_t n, int *rad);
 
 std::string tune_device_name()
 {
@@ -101,55 +103,37 @@ std::vector<std::string> json_objects(const std::string &txt, const std::string 
     return out;
 }
 
-void factor235(int n, int *e2, int *e3, int *e5)
-{
-    *e2 = *e3 = *e5 = 0;
-    while (n % 2 == 0) n /= 2, ++*e2;
-    while (n % 3 == 0) n /= 3, ++*e3;
-    while (n % 5 == 0) n /= 5, ++*e5;
-}
-
-void partitions(int left, int maxpart, std::vector<int> &cur, std::vector<std::vector<int>> &out)
-{
-    if (left == 0) {
-        out.push_back(cur);
-        return;
-    }
-    for (int p = std::min(left, maxpart); p >= 1; --p) {
-        cur.push_back(p);
-        partitions(left - p, p, cur, out);
-        cur.pop_back();
-    }
-}
-
+// Radix orders for rows of N points, the batch's own first: the lists of 2 to 6
+// and 8 with the fewest passes or one more, each descending, ascending and with
+// the odd radices first.
 std::vector<std::vector<int>> row_candidates(int N)
 {
-    int e2, e3, e5;
-    factor235(N, &e2, &e3, &e5);
-    std::vector<std::vector<int>> parts;
+    int def[kMaxPasses];
+    const int ndef = batch_radices(N, def);
+    std::vector<std::vector<int>> out{std::vector<int>(def, def + ndef)};
+    std::set<std::vector<int>> seen{out[0]};
     std::vector<int> cur;
-    partitions(e2, 4, cur, parts);
-    size_t fewest = 100;
-    for (auto &p : parts) fewest = std::min(fewest, p.size());
-    std::set<std::vector<int>> seen;
-    std::vector<std::vector<int>> out;
-    for (auto &p : parts) {
-        if (p.size() > fewest + 1) continue;
-        std::vector<int> two;
-        for (int x : p) two.push_back(1 << x);
-        std::vector<int> odd;
-        for (int i = 0; i < e3; ++i) odd.push_back(3);
-        for (int i = 0; i < e5; ++i) odd.push_back(5);
-        std::vector<int> a = two, b;
-        a.insert(a.end(), odd.begin(), odd.end());           // powers of two first
-        b = odd;
-        b.insert(b.end(), two.begin(), two.end());           // 3s and 5s first
-        std::vector<int> c(a.rbegin(), a.rend());             // reversed
-        for (auto &v : {a, b, c})
-            if (seen.insert(v).second) out.push_back(v);
-    }
+    std::function<void(int, int)> go = [&](int left, int top) {
+        if (left == 1) {
+            std::vector<int> up(cur.rbegin(), cur.rend()), odd = cur;
+            std::stable_partition(odd.begin(), odd.end(), [](int r) { return r % 2 != 0; });
+            for (const auto &v : {cur, up, odd})
+                if (seen.insert(v).second) out.push_back(v);
+            return;
+        }
+        if ((int)cur.size() > ndef) return;
+        for (int r : {8, 6, 5, 4, 3, 2})
+            if (r <= top && left % r == 0) {
+                cur.push_back(r);
+                go(left / r, r);
+                cur.pop_back();
+            }
+    };
+    go(N, 8);
     return out;
 }
+
+constexpr float kMargin = 0.97f;  // of the built-in choice's time, to replace it
 
 struct Timer {
     hipStream_t s = nullptr;
@@ -200,6 +184,7 @@ bool tune_load(const std::string &path, const std::string &device, const std::st
     t.device = json_string(txt, "device");
     t.version = json_string(txt, "version");
     if (t.device != device || t.version != version) return false;
+    t.batch_lists = !json_ints(txt, "radices").empty();
     for (const std::string &o : json_objects(txt, "rows")) {
         auto n = json_ints(o, "n"), rw = json_ints(o, "rows_per_wg"), rad = json_ints(o, "radix");
         if (n.size() != 1 || rw.size() != 1 || rad.empty()) continue;
@@ -229,7 +214,8 @@ bool tune_save(const std::string &path, const TuneTable &t)
 {
     std::ofstream f(path);
     if (!f) return false;
-    f << "{\n  \"device\": \"" << t.device << "\",\n  \"version\": \"" << t.version << "\",\n  \"rows\": [";
+    f << "{\n  \"device\": \"" << t.device << "\",\n  \"version\": \"" << t.version
+      << "\",\n  \"radices\": [2, 3, 4, 5, 6, 8],\n  \"rows\": [";
     bool first = true;
     for (const auto &kv : t.rows) {
         f << (first ? "\n" : ",\n") << "    {\"n\": " << kv.first << ", \"rows_per_wg\": " << kv.second.rows_per_wg
@@ -314,7 +300,7 @@ extern "C" int fft_autotune(int n, const fft_item_desc *items, const char *cache
         }
         int64_t rw0 = 1;
         while (rw0 * 2 <= 256 && rw0 * 2 * N <= 4096) rw0 *= 2;
-        float best = -1.f;
+        float first = -1.f, best = -1.f;
         RowTune win;
         for (const std::vector<int> &rad : row_candidates(N)) {
             for (int64_t rw : {rw0, rw0 / 2}) {
@@ -328,8 +314,10 @@ extern "C" int fft_autotune(int n, const fft_item_desc *items, const char *cache
                 d.lanes_per_row = (int)(256 / rw);
                 d.nrows = cap / N;
                 d.tw = tw;
-                const float ms = tm.time([&] { return launch_fft_rows(d, false, -1, a, b, 1.0, tm.s); }, 5);
-                if (ms > 0.f && (best < 0.f || ms < best)) {
+                const float ms = tm.time([&] { return launch_batch_rows(d, a, b, tm.s); }, 5);
+                if (ms <= 0.f) continue;
+                if (first < 0.f) first = ms;
+                if (best < 0.f || (ms < best && ms < kMargin * first)) {
                     best = ms;
                     win.rows_per_wg = (int)rw;
                     win.radix = rad;
@@ -341,7 +329,7 @@ extern "C" int fft_autotune(int n, const fft_item_desc *items, const char *cache
     for (const auto &pr : pairs) {
         if (rc) break;
         const int Nu = pr.first, Nv = pr.second;
-        float best = -1.f;
+        float first = -1.f, best = -1.f;
         TileTune win;
         const int64_t S = std::max<int64_t>(1, cap / ((int64_t)Nu * Nv));
         for (auto tt : std::vector<std::pair<int, int>>{{64, 64}, {32, 32}, {16, 16}, {64, 16}, {16, 64}, {32, 64},
@@ -365,8 +353,10 @@ extern "C" int fft_autotune(int n, const fft_item_desc *items, const char *cache
             d.tiles_u = (Nu + TU - 1) / TU;
             d.tiles_v = (Nv + TV - 1) / TV;
             d.tiles_g = (S + G - 1) / G;
-            const float ms = tm.time([&] { return launch_xpose(d, 8, a, b, tm.s); }, 5);
-            if (ms > 0.f && (best < 0.f || ms < best)) {
+            const float ms = tm.time([&] { return launch_batch_tile(d, a, b, tm.s); }, 5);
+            if (ms <= 0.f) continue;
+            if (first < 0.f) first = ms;
+            if (best < 0.f || (ms < best && ms < kMargin * first)) {
                 best = ms;
                 win = TileTune{TU, TV, (int)G};
             }
@@ -388,16 +378,9 @@ extern "C" int fft_autotune(int n, const fft_item_desc *items, const char *cache
         x.bsize[0] = S;
         x.ba[0] = x.bb[0] = (int64_t)Nu * Nv;
         x.nslices = S;
-        // the built-in order first; another wins only by a clear margin (3%),
-        // since the times of near-equal orders differ by noise on this array
-        int def[kMaxPasses];
-        const int ndef = factor_radices(Nu, def);
-        std::vector<std::vector<int>> cands{std::vector<int>(def, def + ndef)};
-        for (const std::vector<int> &rad : row_candidates(Nu))
-            if (rad != cands[0]) cands.push_back(rad);
         float fdef = -1.f, fbest = -1.f;
         std::vector<int> fwin;
-        for (const std::vector<int> &rad : cands) {
+        for (const std::vector<int> &rad : row_candidates(Nu)) {
             FftDesc f;
             std::memset(&f, 0, sizeof(f));
             f.N = Nu;
@@ -405,12 +388,12 @@ extern "C" int fft_autotune(int n, const fft_item_desc *items, const char *cache
             for (size_t q = 0; q < rad.size(); ++q) f.radix[q] = rad[q];
             f.nrows = S * Nv;
             f.tw = tw;
-            const float ms = tm.time([&] { return launch_fft_xpose_generic(f, x, false, -1, a, b, 1.0, tm.s); }, 10);
+            const float ms = tm.time([&] { return launch_batch_unit(f, x, a, b, tm.s); }, 10);
             if (ms <= 0.f) continue;
             if (fdef < 0.f) {
                 fdef = fbest = ms;
                 fwin = rad;
-            } else if (ms < fbest && ms < 0.97f * fdef) {
+            } else if (ms < fbest && ms < kMargin * fdef) {
                 fbest = ms;
                 fwin = rad;
             }

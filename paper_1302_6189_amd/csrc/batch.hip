@@ -376,8 +376,6 @@ struct fft_batch_impl {
     bool lean = false;    // every stage a fused unit of radices 2 to 6 and 8 (batch_kernel's LEAN form)
 };
 
-namespace {
-
 // Radices of a batch's step of built-in order: of 2..6 and 8 the fewest
 // passes, then the smallest sum, those with fewer factors 2 first (a first
 // pass of radix r stores with a stride of r values, and strides of many
@@ -410,6 +408,67 @@ int batch_radices(i64 n, int *rad)
     std::copy(best, best + nbest, rad);
     return nbest;
 }
+
+// ---- the batch's stages as kernels of their own, for the autotuner --------------
+template <bool TW_LDS>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4)))
+    batch_unit_kernel(const float2 *in, float2 *out, FftDesc f, XposeDesc d, int rw, int G)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    fft_xpose_unit<float2, -1, TW_LDS, kRadBatch, true, true>(in, out, f, d, rw, G, blockIdx.x, 1.f, false, smem);
+}
+
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3)))
+    batch_rows_kernel(const float2 *in, float2 *out, FftDesc f)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    fft_rows_block<float2, -1, false, kRadBatch>(in, out, f, blockIdx.x, 1.f, false, reinterpret_cast<float2 *>(smem));
+}
+
+template <int VU, int VV>
+__global__ void __launch_bounds__(kThreads) batch_tile_kernel(const float2 *in, float2 *out, XposeDesc d)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    xpose_tile<float2, VU, VV>(in, out, d, blockIdx.x, smem);
+}
+
+hipError_t launch_batch_unit(const FftDesc &f, const XposeDesc &d, const void *in, void *out, hipStream_t s)
+{
+    int rw = 1, G = 1;
+    fused_unit_shape(f.N, 8, d.Nv, d.nslices, 4096, &rw, &G);
+    const bool tw = unit_tw_fits(f.N, 8);
+    const dim3 grid((unsigned)(((d.Nv + rw - 1) / rw) * ((d.nslices + G - 1) / G)));
+    auto kernel = tw ? &batch_unit_kernel<true> : &batch_unit_kernel<false>;
+    hipLaunchKernelGGL(kernel, grid, dim3(kThreads),
+                       fused_unit_bytes(f.N, rw, G, 8, tw), s, (const float2 *)in, (float2 *)out, f, d, rw, G);
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_rows(const FftDesc &f, const void *in, void *out, hipStream_t s)
+{
+    const dim3 grid((unsigned)((f.nrows + f.rows_per_wg - 1) / f.rows_per_wg));
+    hipLaunchKernelGGL(batch_rows_kernel, grid, dim3(kThreads), (size_t)f.rows_per_wg * f.N * 8, s, (const float2 *)in,
+                       (float2 *)out, f);
+    return hipGetLastError();
+}
+
+// 16-byte accesses along even axes, as transpose stages choose them
+int batch_xv(const XposeDesc &d)
+{
+    return ((d.Nu % 2 == 0 && d.TU >= 2) ? 1 : 0) | ((d.Nv % 2 == 0 && d.TV >= 2) ? 2 : 0);
+}
+
+hipError_t launch_batch_tile(const XposeDesc &d, const void *in, void *out, hipStream_t s)
+{
+    const int xv = batch_xv(d);
+    auto kernel = xv == 3 ? &batch_tile_kernel<2, 2> : xv == 1 ? &batch_tile_kernel<2, 1>
+                  : xv == 2 ? &batch_tile_kernel<1, 2> : &batch_tile_kernel<1, 1>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(d.tiles_u * d.tiles_v * d.tiles_g)), dim3(kThreads),
+                       xpose_tile_bytes(d, 8) + 16, s, (const float2 *)in, (float2 *)out, d);
+    return hipGetLastError();
+}
+
+namespace {
 
 int batch_fail_hip(hipError_t e, const char *what)
 {
@@ -498,6 +557,7 @@ int fft_batch_plan(fft_batch_t *out, int n, const fft_item_desc *items, int prec
     size_t lds = 16, lds_tw = 16;  // LDS per group without and with staged twiddles
     bool tw_fits = true;          // every fused step's table fits (unit_tw_fits)
     int max_stage = 0;
+    std::vector<char> listed((size_t)n * kMaxDims, 0);  // the step's radices are the cache's
     for (int i = 0; i < n; ++i) {
         const fft_item_desc &it = items[i];
         fft_plan_t p = nullptr;
@@ -516,6 +576,10 @@ int fft_batch_plan(fft_batch_t *out, int n, const fft_item_desc *items, int prec
         d.nx = nx;
         d.buf[2] = (float2 *)p->work;
         d.inv_scale = (float)(1.0 / (double)p->T);
+        for (int t = 0; tuned && t < it.M; ++t) {
+            auto rt = tune.rows.find(p->fft[t].N);
+            listed[(size_t)i * kMaxDims + t] = rt != tune.rows.end() && valid_radices(rt->second.radix, p->fft[t].N);
+        }
         int64_t units = 0;
         // fused schedule: a unit's shape is fused_unit_shape's
         d.fused = !(flags & FFTRW_FLAG_BATCH_NO_FUSE);
@@ -535,15 +599,10 @@ int fft_batch_plan(fft_batch_t *out, int n, const fft_item_desc *items, int prec
                         auto ft = tune.fused.find({N, (int)d.xp[t].Nv});
                         if (ft != tune.fused.end()) {
                             const std::vector<int> &rad = ft->second;
-                            int64_t prod = 1;
-                            bool ok = !rad.empty() && (int)rad.size() <= kMaxPasses;
-                            for (int r : rad) {
-                                ok = ok && (r == 2 || r == 3 || r == 4 || r == 5 || r == 8 || r == 16);
-                                prod *= r;
-                            }
-                            if (ok && prod == N) {
+                            if (valid_radices(rad, N)) {
                                 d.fft[t].npass = (int)rad.size();
                                 for (int q = 0; q < d.fft[t].npass; ++q) d.fft[t].radix[q] = rad[q];
+                                listed[(size_t)i * kMaxDims + t] = 1;
                             }
                         }
                     }
@@ -589,8 +648,7 @@ int fft_batch_plan(fft_batch_t *out, int n, const fft_item_desc *items, int prec
                 d.dst[st] = other;
                 std::swap(cur, other);
                 d.xp[t] = p->xp[t];
-                d.xv[t] = ((d.xp[t].Nu % 2 == 0 && d.xp[t].TU >= 2) ? 1 : 0) |
-                          ((d.xp[t].Nv % 2 == 0 && d.xp[t].TV >= 2) ? 2 : 0);
+                d.xv[t] = batch_xv(d.xp[t]);
                 units += d.xp[t].tiles_u * d.xp[t].tiles_v * d.xp[t].tiles_g;
                 lds = std::max(lds, xpose_tile_bytes(d.xp[t], 8) + 16);
             }
@@ -640,7 +698,8 @@ int fft_batch_plan(fft_batch_t *out, int n, const fft_item_desc *items, int prec
             FftDesc &f = d.fft[t];
             int rad[kMaxPasses], np = 0;
             int def[kMaxPasses];
-            if (f.npass == factor_radices(f.N, def) && std::equal(def, def + f.npass, f.radix)) {
+            if (!listed[(size_t)i * kMaxDims + t] ||
+                (!tune.batch_lists && f.npass == factor_radices(f.N, def) && std::equal(def, def + f.npass, f.radix))) {
                 f.npass = batch_radices(f.N, f.radix);
                 continue;
             }

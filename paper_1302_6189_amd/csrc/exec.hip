@@ -154,13 +154,7 @@ int make_len_desc(fft_plan_impl *pl, i64 N, FftDesc *d, bool generic_rows, const
         auto it = tune->rows.find((int)N);
         if (it != tune->rows.end()) {
             const RowTune &rt = it->second;
-            i64 prod = 1;
-            bool ok = !rt.radix.empty() && (int)rt.radix.size() <= kMaxPasses;
-            for (int r : rt.radix) {
-                ok = ok && (r == 2 || r == 3 || r == 4 || r == 5 || r == 8 || r == 16);
-                prod *= r;
-            }
-            if (ok && prod == N) {
+            if (valid_radices(rt.radix, N)) {
                 d->npass = (int)rt.radix.size();
                 for (int q = 0; q < d->npass; ++q) d->radix[q] = rt.radix[q];
             }

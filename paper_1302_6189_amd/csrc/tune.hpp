@@ -7,7 +7,21 @@
 #include <utility>
 #include <vector>
 
+#include "kernels.hpp"
+
 namespace fftrw {
+
+// a radix list the batch's kernel runs (16 as 4 x 4) for rows of N points
+inline bool valid_radices(const std::vector<int> &rad, int64_t N)
+{
+    int64_t prod = 1;
+    bool ok = !rad.empty() && (int)rad.size() <= kMaxPasses;
+    for (int r : rad) {
+        ok = ok && (r == 2 || r == 3 || r == 4 || r == 5 || r == 6 || r == 8 || r == 16);
+        prod *= r;
+    }
+    return ok && prod == N;
+}
 
 struct RowTune {
     int rows_per_wg = 0;      // 0: built-in choice
@@ -20,6 +34,9 @@ struct TileTune {
 
 struct TuneTable {
     std::string device, version;
+    // lists timed in the batch's own kernels against its built-in ones (the
+    // file says with which radices); those of older files were timed in others
+    bool batch_lists = false;
     std::map<int, RowTune> rows;                       // by row length
     std::map<std::pair<int, int>, TileTune> tiles;     // by (Nu, Nv)
     std::map<std::pair<int, int>, std::vector<int>> fused;  // radix order of a fused step, by (N, Nv)
