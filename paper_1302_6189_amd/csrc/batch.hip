@@ -262,14 +262,14 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(L
             publish();
             if (it.fused) {
                 const bool last = st == it.M - 1;
-                fft_rows_block<float2, DIR, false, kRadBatch>(src, dst, it.fft[st], local, DIR > 0 && last ? it.inv_scale : 1.f,
+                fft_rows_block<float2, DIR, kRadBatch>(src, dst, it.fft[st], local, DIR > 0 && last ? it.inv_scale : 1.f,
                                             DIR > 0 && last, reinterpret_cast<float2 *>(smem));
                 continue;
             }
             const int t = st >> 1;
             if ((st & 1) == 0) {
                 const bool last = t == it.M - 1;
-                fft_rows_block<float2, DIR, false, kRadBatch>(src, dst, it.fft[t], local, DIR > 0 && last ? it.inv_scale : 1.f,
+                fft_rows_block<float2, DIR, kRadBatch>(src, dst, it.fft[t], local, DIR > 0 && last ? it.inv_scale : 1.f,
                                             DIR > 0 && last, reinterpret_cast<float2 *>(smem));
             } else {
                 switch (it.xv[t]) {
@@ -422,7 +422,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3
     batch_rows_kernel(const float2 *in, float2 *out, FftDesc f)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    fft_rows_block<float2, -1, false, kRadBatch>(in, out, f, blockIdx.x, 1.f, false, reinterpret_cast<float2 *>(smem));
+    fft_rows_block<float2, -1, kRadBatch>(in, out, f, blockIdx.x, 1.f, false, reinterpret_cast<float2 *>(smem));
 }
 
 template <int VU, int VV>

@@ -34,8 +34,8 @@ int count_beside(const XposeDesc &d, int threads);
 hipError_t launch_count(const XposeDesc &d, hipStream_t s);
 hipError_t launch_ct_rows(int N, bool fp64, const void *tw, int64_t nrows, int dir, const void *in, void *out,
                           double scale, CachePolicy policy, hipStream_t s);
-hipError_t launch_fft_xpose_generic(const FftDesc &f, const XposeDesc &d, bool fp64, int dir, const void *in,
-                                    void *out, double scale, hipStream_t s);
+hipError_t launch_xpose_points(const FftDesc &f, const XposeDesc &d, bool fp64, const void *in, void *out, double scale,
+                               hipStream_t s);
 hipError_t launch_fft_mfma_xpose(int precision, int dir, int N, const void *twN, const XposeDesc &d, const void *in,
                                  void *out, double scale, bool nt_store, hipStream_t s);
 hipError_t launch_fft_mfma(int precision, int dir, int N, const void *twN, int64_t nrows, const void *in, void *out,
@@ -414,8 +414,7 @@ int run_fused_step(fft_plan_impl *pl, int t, int nx, int dir, const void *src, v
                                       cache_policy(pl, t == nx - 1, x.Nv % 16 == 0).nt_store, s),
                 "fused mfma fft+transpose launch");
     } else {
-        // single points: the run-time-radix unit
-        HIP_TRY(launch_fft_xpose_generic(d, x, pl->esz == 16, dir, src, dst, scale, s), "fused fft+transpose launch");
+        HIP_TRY(launch_xpose_points(d, x, pl->esz == 16, src, dst, scale, s), "fused fft+transpose launch");
     }
     return FFTRW_OK;
 }
@@ -709,7 +708,7 @@ int plan_create(fft_plan_t *plan, int M, const int64_t *dims, int64_t P, const i
     }
     // fusion of every FFT step with its transpose (the default): rows of 2 to
     // 4096 points (complex128: 2048) use the compile-time kernel of their
-    // length, single points the run-time-radix unit, steps of the
+    // length, single points a unit without passes, steps of the
     // split-precision form (256 and 512 points) the MFMA kernel
     if (!(flags & (FFTRW_FLAG_SEPARATE | FFTRW_FLAG_STAGED)) && !generic_rows) {
         const bool fp64 = pl->esz == 16;
@@ -722,8 +721,7 @@ int plan_create(fft_plan_t *plan, int M, const int64_t *dims, int64_t P, const i
             const bool ct_ok = d.ct && !d.mfma &&
                                (pl->precision == FFTRW_PREC_NATIVE || d.N <= 512 || (d.N & (d.N - 1)) != 0) &&
                                ct_plan_step(d.N, fp64, pl->xp[t], &pl->ct_step[t]);
-            const bool generic_ok = !d.ct && !d.mfma && d.N + 1 <= (fp64 ? 2048 : 4096);
-            pl->fuse_kind[t] = d.mfma ? 3 : (ct_ok ? 1 : (generic_ok ? 2 : 0));
+            pl->fuse_kind[t] = d.mfma ? 3 : ct_ok ? 1 : d.N == 1 ? 2 : 0;
             ok = pl->fuse_kind[t] != 0;
         }
         pl->fused = ok;

@@ -567,13 +567,8 @@ __device__ __forceinline__ void ct_store_runs(C *out, const C *lds, const CtShap
         split(e, gi, k, r);
         if (e < total) {
             const int col = gi * s.rw + r;
-            const C *l = lds + k * s.sp;
-            if constexpr (W == 2) {
-                // (rw is even: a pair shares its 128 bytes)
-                q[it] = value(l + ct_col<C>(col));
-            } else {
-                q[it] = value(l + ct_col<C>(col));
-            }
+            // (with pairs rw is even: a pair shares its 128 bytes)
+            q[it] = value(lds + k * s.sp + ct_col<C>(col));
         }
     }
 #pragma unroll

@@ -11,7 +11,8 @@
 namespace fftrw {
 
 // Every 2,3,5-smooth length from 2 to kCtMax (complex64) or kCtMaxFp64
-// (complex128): the lengths a plan accepts.
+// (complex128).  Plans accept lengths up to 4096 in both: complex128 rows past
+// kCtMaxFp64 run the run-time-radix kernel, in plans of separate kernels.
 constexpr int kCtMax = 4096;
 constexpr int kCtMaxFp64 = 2048;
 
@@ -41,8 +42,8 @@ constexpr int kCtLengths = kCtLengthTable.count;
 constexpr int ct_length(int i) { return kCtLengthTable.n[i]; }
 
 // Exact n / d for n < 2^31 by a multiply: m = floor(2^(31 + l) / d) + 1 with
-// l = ceil(log2 d) exceeds 2^(31 + l) / d by at most 2^l / d / 2^l, which adds
-// less than n / 2^31 / d < 1 / d to n / d.  (d = 1: m = 0, one = ~0.)
+// l = ceil(log2 d) exceeds 2^(31 + l) / d by at most 1, which adds at most
+// n / 2^(31 + l) < 1 / 2^l <= 1 / d to n / d.  (d = 1: m = 0, one = ~0.)
 struct CtDiv {
     uint32_t m, s, one;
     __device__ __forceinline__ uint32_t operator()(uint32_t n) const { return (__umulhi(n, m) + (n & one)) >> s; }

@@ -1,6 +1,8 @@
-// fft_rows.hip -- stand-alone launch of the generic row FFT (fft_generic.hpp)
-// for 2,3,5-smooth lengths, the FP64 twiddle table w_N^e it reads, and the
-// fused unit's shape rule exported for tests (fft_fused_unit_shape).
+// fft_rows.hip -- the FP64-generated twiddle tables w_N^e of the run-time-radix
+// kernels, and the launches of those that plans still reach: rows of complex128
+// past the compile-time kernels (2049 to 4096 points) and steps of single
+// points.  The fused unit's shape rule exported for tests
+// (fft_fused_unit_shape).
 #include <hip/hip_runtime.h>
 
 #include "../../include/fftrw.h"
@@ -31,18 +33,17 @@ hipError_t launch_twiddles(void *out, int64_t n, bool fp64, hipStream_t s)
     return hipGetLastError();
 }
 
-template <typename C, int DIR, bool TW_LDS, bool LEAN>
+template <typename C, int DIR, bool LEAN>
 __global__ void __launch_bounds__(kThreads)
     fft_rows_kernel(const C *in, C *out, FftDesc d, typename RealOf<C>::type scale, int do_scale)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    fft_rows_block<C, DIR, TW_LDS, LEAN ? kRadSmall : kRadRows>(in, out, d, blockIdx.x, scale, do_scale != 0, reinterpret_cast<C *>(smem_raw));
+    fft_rows_block<C, DIR, LEAN ? kRadSmall : kRadRows>(in, out, d, blockIdx.x, scale, do_scale != 0,
+                                                        reinterpret_cast<C *>(smem_raw));
 }
 
-// Radix lists without 8 and 16 (lengths with at most two factors 2, or the
-// lists the autotuner picks that way) run the kernels compiled for radices 2
-// to 5 only: the same passes with fewer registers (complex64 118-119 VGPRs
-// instead of 131-135, four waves per SIMD instead of three).
+// Radix lists without 8 and 16 (lengths with at most two factors 2) run the
+// kernel compiled for radices 2 to 5 only.
 bool lean_radices(const FftDesc &d)
 {
     for (int q = 0; q < d.npass; ++q)
@@ -55,86 +56,53 @@ hipError_t launch_fft_rows(const FftDesc &d, bool fp64, int dir, const void *in,
 {
     const int64_t nblk = (d.nrows + d.rows_per_wg - 1) / d.rows_per_wg;
     if (nblk <= 0) return hipSuccess;
-    const size_t esz = fp64 ? 16 : 8;
-    // the twiddle table goes to LDS after the rows when it takes at most 16 KB
-    const bool tw = unit_tw_fits(d.N, esz);
-    const size_t lds = ((size_t)d.rows_per_wg * d.N + (tw ? d.N : 0)) * esz;
+    const size_t lds = (size_t)d.rows_per_wg * d.N * (fp64 ? 16 : 8);
     const int do_scale = scale != 1.0;
     dim3 grid((unsigned)nblk), block(kThreads);
-    const bool lean = lean_radices(d);
-#define FFTRW_LAUNCH(C, D, T, SC)                                                                                  \
-    do {                                                                                                         \
-        if (lean)                                                                                                \
-            hipLaunchKernelGGL((fft_rows_kernel<C, D, T, true>), grid, block, lds, s, (const C *)in, (C *)out, d, SC, \
-                               do_scale);                                                                        \
-        else                                                                                                     \
-            hipLaunchKernelGGL((fft_rows_kernel<C, D, T, false>), grid, block, lds, s, (const C *)in, (C *)out, d, SC, \
-                               do_scale);                                                                        \
-    } while (0)
-    if (fp64) {
-        if (dir < 0) {
-            if (tw) FFTRW_LAUNCH(double2, -1, true, scale); else FFTRW_LAUNCH(double2, -1, false, scale);
-        } else {
-            if (tw) FFTRW_LAUNCH(double2, 1, true, scale); else FFTRW_LAUNCH(double2, 1, false, scale);
-        }
+#define FFTRW_LAUNCH(C, D, L, SC) \
+    hipLaunchKernelGGL((fft_rows_kernel<C, D, L>), grid, block, lds, s, (const C *)in, (C *)out, d, SC, do_scale)
+    if (d.N == 1) {  // scaled copies: no direction
+        if (fp64) FFTRW_LAUNCH(double2, -1, true, scale); else FFTRW_LAUNCH(float2, -1, true, (float)scale);
+    } else if (!fp64) {
+        return hipErrorInvalidValue;  // compile-time kernels
+    } else if (lean_radices(d)) {
+        if (dir < 0) FFTRW_LAUNCH(double2, -1, true, scale); else FFTRW_LAUNCH(double2, 1, true, scale);
     } else {
-        if (dir < 0) {
-            if (tw) FFTRW_LAUNCH(float2, -1, true, (float)scale); else FFTRW_LAUNCH(float2, -1, false, (float)scale);
-        } else {
-            if (tw) FFTRW_LAUNCH(float2, 1, true, (float)scale); else FFTRW_LAUNCH(float2, 1, false, (float)scale);
-        }
+        if (dir < 0) FFTRW_LAUNCH(double2, -1, false, scale); else FFTRW_LAUNCH(double2, 1, false, scale);
     }
 #undef FFTRW_LAUNCH
     return hipGetLastError();
 }
 
-template <typename C, int DIR, bool TW_LDS, bool LEAN>
+template <typename C>
 __global__ void __launch_bounds__(kThreads)
-    fft_xpose_generic_kernel(const C *in, C *out, FftDesc f, XposeDesc d, int rw, int G,
-                             typename RealOf<C>::type scale, int do_scale)
+    xpose_points_kernel(const C *in, C *out, FftDesc f, XposeDesc d, int rw, int G, typename RealOf<C>::type scale,
+                        int do_scale)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    fft_xpose_unit<C, DIR, TW_LDS, LEAN ? kRadSmall : kRadRows>(in, out, f, d, rw, G, blockIdx.x, scale, do_scale != 0, smem_raw);
+    fft_xpose_unit<C, -1, true, kRadSmall>(in, out, f, d, rw, G, blockIdx.x, scale, do_scale != 0, smem_raw);
 }
 
-// one FFT step of 2,3,5-smooth rows fused with the transpose that follows
-hipError_t launch_fft_xpose_generic(const FftDesc &f, const XposeDesc &d, bool fp64, int dir, const void *in,
-                                    void *out, double scale, hipStream_t s)
+// a step of single points fused with the transpose that follows
+hipError_t launch_xpose_points(const FftDesc &f, const XposeDesc &d, bool fp64, const void *in, void *out, double scale,
+                               hipStream_t s)
 {
+    if (f.N != 1) return hipErrorInvalidValue;
     const size_t esz = fp64 ? 16 : 8;
     int rw = 1, G = 1;
     fused_unit_shape(f.N, esz, d.Nv, d.nslices, fp64 ? 2048 : 4096, &rw, &G);
     const int64_t nblk = ((d.Nv + rw - 1) / rw) * ((d.nslices + G - 1) / G);
     if (nblk <= 0) return hipSuccess;
     if (nblk >= (int64_t)0x7fffffff) return hipErrorInvalidValue;
-    const bool tw = unit_tw_fits(f.N, esz);
-    const size_t lds = fused_unit_bytes(f.N, rw, G, esz, tw);
+    const size_t lds = fused_unit_bytes(f.N, rw, G, esz, true);
     const int do_scale = scale != 1.0;
     dim3 grid((unsigned)nblk), block(kThreads);
-    const bool lean = lean_radices(f);
-#define FFTRW_LAUNCH(C, D, T, SC)                                                                             \
-    do {                                                                                                    \
-        if (lean)                                                                                           \
-            hipLaunchKernelGGL((fft_xpose_generic_kernel<C, D, T, true>), grid, block, lds, s, (const C *)in, \
-                               (C *)out, f, d, rw, G, SC, do_scale);                                        \
-        else                                                                                                \
-            hipLaunchKernelGGL((fft_xpose_generic_kernel<C, D, T, false>), grid, block, lds, s, (const C *)in, \
-                               (C *)out, f, d, rw, G, SC, do_scale);                                        \
-    } while (0)
-    if (fp64) {
-        if (dir < 0) {
-            if (tw) FFTRW_LAUNCH(double2, -1, true, scale); else FFTRW_LAUNCH(double2, -1, false, scale);
-        } else {
-            if (tw) FFTRW_LAUNCH(double2, 1, true, scale); else FFTRW_LAUNCH(double2, 1, false, scale);
-        }
-    } else {
-        if (dir < 0) {
-            if (tw) FFTRW_LAUNCH(float2, -1, true, (float)scale); else FFTRW_LAUNCH(float2, -1, false, (float)scale);
-        } else {
-            if (tw) FFTRW_LAUNCH(float2, 1, true, (float)scale); else FFTRW_LAUNCH(float2, 1, false, (float)scale);
-        }
-    }
-#undef FFTRW_LAUNCH
+    if (fp64)
+        hipLaunchKernelGGL(xpose_points_kernel<double2>, grid, block, lds, s, (const double2 *)in, (double2 *)out, f, d, rw,
+                           G, scale, do_scale);
+    else
+        hipLaunchKernelGGL(xpose_points_kernel<float2>, grid, block, lds, s, (const float2 *)in, (float2 *)out, f, d, rw, G,
+                           (float)scale, do_scale);
     return hipGetLastError();
 }
 

@@ -1,6 +1,6 @@
 // fused_generic.hpp -- one FFT step fused with the transpose that follows it,
-// for rows of any 2,3,5-smooth length (device code shared by single plans and
-// the persistent batched kernel).
+// for rows of any 2,3,5-smooth length (device code of the persistent batched
+// kernel, and of single plans' steps of single points).
 //
 // A unit takes RW rows of layout A that are consecutive in v (the last axis of
 // the next layout B) in each of G consecutive batch slices (G > 1 when the
@@ -247,7 +247,7 @@ struct NoHook {
 // when the level's end writes it back).  hook() runs once the unit's rows are in LDS, after a barrier that every
 // thread passed after entering the unit; no HBM access of the unit's is in
 // flight then except the owner-count atomics.
-template <typename C, int DIR, bool TW_LDS, unsigned RADICES = kRadRows, bool OFF32 = false, bool CACHED = false,
+template <typename C, int DIR, bool TW_LDS, unsigned RADICES, bool OFF32 = false, bool CACHED = false,
           typename Hook = NoHook>
 __device__ __forceinline__ void fft_xpose_unit(const C *__restrict__ in, C *__restrict__ out, const FftDesc &f,
                                                const XposeDesc &d, int rw, int G, int64_t unit,
@@ -331,9 +331,6 @@ __device__ __forceinline__ void fft_xpose_unit(const C *__restrict__ in, C *__re
             break;
         case 8:
             if constexpr (RADICES >> 8 & 1) stockham_pass<8, DIR>(lrow, N, Ns, lanes, lane, tw, wave);
-            break;
-        case 16:
-            if constexpr (RADICES >> 16 & 1) stockham_pass<16, DIR>(lrow, N, Ns, lanes, lane, tw, wave);
             break;
         default: break;
         }

@@ -6,7 +6,7 @@
 namespace fftrw {
 
 constexpr int kMaxPasses = 12;
-constexpr int kThreads = 256;  // work-group size of every kernel here (4 waves of 64)
+constexpr int kThreads = 256;  // work-group size (4 waves of 64), but of the compile-time rows (64 to 1024)
 
 // A device owner-change counter is kCountBlock words whose sum is the count.
 // Kernels that add to it use kCountSlots partial sums on separate 128-byte

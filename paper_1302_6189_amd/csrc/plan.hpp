@@ -90,7 +90,7 @@ struct fft_plan_impl {
     size_t dev_bytes = 0;
     bool executed = false;
     bool fused = false;                 // FFT steps fused with the following transpose
-    int fuse_kind[kMaxDims] = {};       // per step: 1 compile-time kernel, 2 run-time-radix unit, 3 MFMA kernel
+    int fuse_kind[kMaxDims] = {};       // per step: 1 compile-time kernel, 2 single points, 3 MFMA kernel
     CtStep ct_step[kMaxDims];           // launches of the steps of kind 1
 
     // per-stage timing events (fft_plan_set_timing)
