@@ -323,18 +323,26 @@ CachePolicy cache_policy(const fft_plan_impl *pl, bool last, bool whole_lines)
             whole_lines && (bytes >= (size_t)1000000000 || bytes <= ((size_t)20 << 20) || last)};
 }
 
-// ... of rows alone, in a plan of separate kernels or a step by itself.  Stores
-// stream.  So do loads, but of the smallest arrays and of those from the L2s'
-// size to the Infinity Cache's.  Forward transforms in separate kernels,
-// streaming / cached loads: 64x64x512 (17 MB) 44 / 56 us, 128^3 (17 MB) 44 / 46,
-// 4096x1024 (34 MB) 58 / 53, 256^3 (134 MB) 287 / 250, 405^3 (531 MB) 1394 / 1524.
-CachePolicy rows_policy(const fft_plan_impl *pl)
+// ... of rows alone, by what runs around them: a step by itself, a plan of
+// separate kernels, or fused steps (the last step of LEAVE_PERMUTED).
+// Between separate kernels loads are cached below 4 MB and from 24 MB, where
+// they find what the transpose before stored, to 256 MB; stores are cached from
+// 24 MB, for the transpose after, to 1 GB if they are whole lines.  Forward
+// transforms, streaming both / cached both: 64x64x512 (17 MB) 44 / 58 us, 128^3
+// (17 MB) 44 / 48, 4096x1024 (34 MB) 58 / 51, 256^3 (134 MB) 287 / 238, 405^3
+// (531 MB) 1394 / 1570; streaming loads, streaming / cached stores: 256^3
+// complex128 492 / 468, 480^3 1908 / 1882.
+enum RowsUse { kStepAlone, kBetweenTransposes, kAfterFused };
+CachePolicy rows_policy(const fft_plan_impl *pl, int N, RowsUse use)
 {
-    const size_t bytes = (size_t)pl->T * pl->esz;
-    return {bytes > ((size_t)256 << 20) || (bytes > ((size_t)4 << 20) && bytes <= ((size_t)24 << 20)), true};
+    if (use == kAfterFused) return cache_policy(pl, false, true);
+    const size_t bytes = (size_t)pl->T * pl->esz, mb = (size_t)1 << 20;
+    const bool small = bytes <= 24 * mb, large = bytes > 256 * mb, whole = N * pl->esz % 128 == 0;
+    return {large || (small && bytes > 4 * mb),
+            use == kStepAlone || small || (large && (!whole || bytes >= (size_t)1000000000))};
 }
 
-int run_fft_desc(fft_plan_impl *pl, const FftDesc &d, int dir, const void *in, void *out, double scale,
+int run_fft_desc(fft_plan_impl *pl, const FftDesc &d, int dir, const void *in, void *out, double scale, RowsUse use,
                  hipStream_t s)
 {
     if (d.mfma) {
@@ -342,7 +350,7 @@ int run_fft_desc(fft_plan_impl *pl, const FftDesc &d, int dir, const void *in, v
         return FFTRW_OK;
     }
     if (d.ct) {
-        HIP_TRY(launch_ct_rows(d.N, pl->esz == 16, d.tw, d.nrows, dir, in, out, scale, rows_policy(pl), s),
+        HIP_TRY(launch_ct_rows(d.N, pl->esz == 16, d.tw, d.nrows, dir, in, out, scale, rows_policy(pl, d.N, use), s),
                 "fft pass launch");
         return FFTRW_OK;
     }
@@ -368,16 +376,16 @@ int run_split_step(fft_plan_impl *pl, int t, int dir, const void *in, void *out,
         HIP_TRY(launch_bx_butterfly(fp64, dir, out, pl->recv, pl->T, N, h, sp.tw, s), "split-row butterflies");
     }
     if (sp.b > 1)
-        if (int rc = run_fft_desc(pl, sp.local, dir, out, out, 1.0, s)) return rc;
+        if (int rc = run_fft_desc(pl, sp.local, dir, out, out, 1.0, kBetweenTransposes, s)) return rc;
     HIP_TRY(launch_bx_unscramble(fp64, out, pl->recv, pl->T, N, sp.b, sp.s, scale, s), "split-row order");
     HIP_TRY(hipMemcpyAsync(out, pl->recv, (size_t)pl->T * pl->esz, hipMemcpyDeviceToDevice, s), "split-row copy");
     return FFTRW_OK;
 }
 
-int run_fft_step(fft_plan_impl *pl, int t, int dir, const void *in, void *out, double scale, hipStream_t s)
+int run_fft_step(fft_plan_impl *pl, int t, int dir, const void *in, void *out, double scale, RowsUse use, hipStream_t s)
 {
     if (!pl->split.empty() && pl->split[t].c > 0) return run_split_step(pl, t, dir, in, out, scale, s);
-    return run_fft_desc(pl, pl->fft[t], dir, in, out, scale, s);
+    return run_fft_desc(pl, pl->fft[t], dir, in, out, scale, use, s);
 }
 
 int run_transpose(fft_plan_impl *pl, int t, const void *in, void *out, hipStream_t s)
@@ -450,7 +458,7 @@ int run_pipeline(fft_plan_impl *pl, const void *in, void *out, hipStream_t s, in
         }
         if (leave) {
             const double scale = dir > 0 ? 1.0 / (double)pl->T : 1.0;
-            if (int rc = run_fft_step(pl, M - 1, dir, src, out, scale, s)) return rc;
+            if (int rc = run_fft_step(pl, M - 1, dir, src, out, scale, kAfterFused, s)) return rc;
             if (int rc = mark()) return rc;
         }
         pl->n_recorded = nev;
@@ -462,7 +470,7 @@ int run_pipeline(fft_plan_impl *pl, const void *in, void *out, hipStream_t s, in
     void *cur = b0, *other = b1;
     for (int t = 0; t < M; ++t) {
         const double scale = (dir > 0 && t == M - 1) ? 1.0 / (double)pl->T : 1.0;
-        int rc = run_fft_step(pl, t, dir, t == 0 ? in : cur, cur, scale, s);
+        int rc = run_fft_step(pl, t, dir, t == 0 ? in : cur, cur, scale, kBetweenTransposes, s);
         if (rc || (rc = mark())) return rc;
         if (t < nx) {
             if (pl->timing && (pl->flags & FFTRW_FLAG_STAGED) && pl->xp_staged[t]) {
@@ -789,7 +797,7 @@ int fft_exec_fft_step(fft_plan_t plan, int t, int direction, const void *in, voi
     if (!plan || !in || !out) return fail(FFTRW_E_ARG, "null plan or buffer");
     if (t < 0 || t >= plan->M) return fail(FFTRW_E_ARG, "step out of range");
     if (direction != -1 && direction != 1) return fail(FFTRW_E_ARG, "direction must be -1 or +1");
-    return run_fft_step(plan, t, direction, in, out, 1.0, (hipStream_t)stream);
+    return run_fft_step(plan, t, direction, in, out, 1.0, kStepAlone, (hipStream_t)stream);
 }
 
 int fft_exec_transpose(fft_plan_t plan, int t, const void *in, void *out, void *stream)
