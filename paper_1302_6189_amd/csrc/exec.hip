@@ -323,23 +323,29 @@ CachePolicy cache_policy(const fft_plan_impl *pl, bool last, bool whole_lines)
             whole_lines && (bytes >= (size_t)1000000000 || bytes <= ((size_t)20 << 20) || last)};
 }
 
-// ... of rows alone, by what runs around them: a step by itself, a plan of
-// separate kernels, or fused steps (the last step of LEAVE_PERMUTED).
+// ... of rows alone, by what runs around them: a step by itself, the first and
+// the later steps of a plan of separate kernels, or fused steps (before the last
+// step of LEAVE_PERMUTED).
 // Between separate kernels loads are cached below 4 MB and from 24 MB, where
-// they find what the transpose before stored, to 256 MB; stores are cached from
-// 24 MB, for the transpose after, to 1 GB if they are whole lines.  Forward
-// transforms, streaming both / cached both: 64x64x512 (17 MB) 44 / 58 us, 128^3
-// (17 MB) 44 / 48, 4096x1024 (34 MB) 58 / 51, 256^3 (134 MB) 287 / 238, 405^3
-// (531 MB) 1394 / 1570; streaming loads, streaming / cached stores: 256^3
-// complex128 492 / 468, 480^3 1908 / 1882.
-enum RowsUse { kStepAlone, kBetweenTransposes, kAfterFused };
+// they find what the transpose before stored, to 320 MB (256 MB in parts of
+// lines), but above 64 MB not for the input, nor beside the send and receive
+// arrays of a staged plan, of which the caches hold too little; stores are
+// cached from 24 MB, for the transpose after, to 1 GB if they are whole lines.
+// Forward transforms on changing buffers, streaming both / cached both / this
+// rule: 64x64x512 (17 MB) 46 / 60 / 46 us, 256^3 (134 MB) 287 / 244 / 244, staged
+// with N_p = 512 620 / 621 / 596, 256^3 complex128 571 / 477 / 460, 405^3 (531
+// MB) 1439 / 1568 / 1439.
+enum RowsUse { kStepAlone, kFirstStep, kBetweenTransposes, kAfterFused };
 CachePolicy rows_policy(const fft_plan_impl *pl, int N, RowsUse use)
 {
     if (use == kAfterFused) return cache_policy(pl, false, true);
     const size_t bytes = (size_t)pl->T * pl->esz, mb = (size_t)1 << 20;
-    const bool small = bytes <= 24 * mb, large = bytes > 256 * mb, whole = N * pl->esz % 128 == 0;
-    return {large || (small && bytes > 4 * mb),
-            use == kStepAlone || small || (large && (!whole || bytes >= (size_t)1000000000))};
+    const bool small = bytes <= 24 * mb, whole = N * pl->esz % 128 == 0;
+    const size_t held = use == kFirstStep || (use == kBetweenTransposes && (pl->flags & FFTRW_FLAG_STAGED)) ? 64 * mb
+                        : use == kBetweenTransposes && whole                                                ? 320 * mb
+                                                                                                            : 256 * mb;
+    return {bytes > held || (small && bytes > 4 * mb),
+            use == kStepAlone || small || (bytes > 256 * mb && (!whole || bytes >= (size_t)1000000000))};
 }
 
 int run_fft_desc(fft_plan_impl *pl, const FftDesc &d, int dir, const void *in, void *out, double scale, RowsUse use,
@@ -470,7 +476,7 @@ int run_pipeline(fft_plan_impl *pl, const void *in, void *out, hipStream_t s, in
     void *cur = b0, *other = b1;
     for (int t = 0; t < M; ++t) {
         const double scale = (dir > 0 && t == M - 1) ? 1.0 / (double)pl->T : 1.0;
-        int rc = run_fft_step(pl, t, dir, t == 0 ? in : cur, cur, scale, kBetweenTransposes, s);
+        int rc = run_fft_step(pl, t, dir, t == 0 ? in : cur, cur, scale, t == 0 ? kFirstStep : kBetweenTransposes, s);
         if (rc || (rc = mark())) return rc;
         if (t < nx) {
             if (pl->timing && (pl->flags & FFTRW_FLAG_STAGED) && pl->xp_staged[t]) {
