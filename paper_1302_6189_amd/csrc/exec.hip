@@ -309,8 +309,10 @@ int dev_alloc(fft_plan_impl *pl, void **p, size_t bytes)
 // 160^3 (33 MB) 40 / 44 us, 192^3 (57 MB) 63 / 64, 240^3 121 / 112, 288^3
 // 240 / 199, 512^3 1167 / 1137.
 // Stores are cached except
-//   * from 1 GB on, where little of them survives (streaming / cached:
-//     480^3 1047 / 1038, 512^3 1137 / 1162);
+//   * from 1 GB on, where little of them survives (streaming over cached time of
+//     cubes: 1.18 at 262 MB, 1.07 at 453, 1.02 at 645, 1.005 at 885, 0.99 at 1074,
+//     1.00 at 1.5 to 2.1 GB, 0.99 at 3.0 and 3.6; 128x128x128x64, 1074 MB, 0.985,
+//     1024x1024x128 1.03);
 //   * while the L2s hold the array, as dirty lines are written back when a
 //     kernel ends (96^3 17.9 / 19.8, 128^3 25.4 / 27.5; 144^3 42.7 / 37.8);
 //   * in the last step, whose output no later step reads (256^3 131.9 / 139.8);

@@ -995,7 +995,9 @@ StagedTile tile_args(const fft_plan_impl *pl, const StagedStep &st, const Staged
 // the Infinity Cache's size, loads cached below 64 MB).  Staged forward
 // transforms, all streaming / this rule: 200^3 N_p = 64 609 / 415 us, 320^3
 // N_p = 100 2057 / 1390, 256^3 N_p = 512 652 / 608; all cached at 512^3,
-// N_p = 4096: 5184 us against 4871 streaming.
+// N_p = 4096: 5184 us against 4871 streaming.  Stores alone, streaming over
+// cached time of cubes: 1.02 at 134 MB, 0.97 and 1.005 at 262 (N_p = 512, 64),
+// 0.95 at 453, 0.98 at 645, 0.99 at 885 and 1074.
 void staged_policy(const fft_plan_impl *pl, const StagedStep &st, const XposeDesc &d, CachePolicy *segments,
                    CachePolicy *rows)
 {
