@@ -278,6 +278,8 @@ constexpr int64_t kStraightBytes = 4 << 20;
 // 625 points 39 and 42).
 constexpr int64_t kBlockRowBytes = 1024, kBlockBytes = (int64_t)256 << 20;
 
+constexpr int64_t kFewGroups = 448;
+
 hipError_t launch_ct_rows(int N, bool fp64, const void *tw, int64_t nrows, int dir, const void *in, void *out,
                           double scale, CachePolicy policy, hipStream_t s)
 {
@@ -288,12 +290,16 @@ hipError_t launch_ct_rows(int N, bool fp64, const void *tw, int64_t nrows, int d
     // groups of 256 threads, or smaller ones where the chip then holds more
     // waves (625 points, whose padded rows leave LDS for two groups of 256
     // threads: 42.7 us for 134 MB, 39.2 in groups of 64) or would have few groups
+    // (128 points, 256 threads / fewer: 1 MB 3.72 / 3.12 us, 12 MB, 1.4 groups a
+    // compute unit, 6.72 / 5.56, but 16 MB, 1.9 groups, 6.32 / 7.24).  Rows of one
+    // lane that all fit one group stay in it (256 rows of 4 points 1.48 / 1.76).
     auto resident = [&](int t) {
         return std::min<int64_t>((int64_t)(kLdsBytes / ((size_t)(t / e->L) * e->pitch * e->esz)) * t, 1024);
     };
     int threads = std::max(256, e->min_threads);
     while (threads > e->min_threads &&
-           (resident(threads / 2) > resident(threads) || nrows * e->L / threads < 512))
+           (resident(threads / 2) > resident(threads) ||
+            (nrows * e->L / threads < kFewGroups && (e->L > 1 || nrows > threads))))
         threads /= 2;
     const int rows = threads / e->L;
     while ((1 << c.lr) < rows) ++c.lr;

@@ -56,6 +56,18 @@ def test_sizes_agree(gpu_lib, n, double):
             del big, out
 
 
+# rows of one lane that fit one group, whole and ragged, and one row more
+@pytest.mark.parametrize("rows", [1, 27, 250, 256, 270])
+@pytest.mark.parametrize("n", [2, 4, 9, 16])
+def test_one_group(gpu_lib, rows, n):
+    import torch
+    x = inputs.gaussian((rows, n), rows * n, np.complex64)
+    xd = to_dev(x)
+    out = torch.empty_like(xd)
+    _step((rows, n), fftrw.C64, xd, out, -1)
+    assert dft.rel_l2(to_host(out), dft.fft1d_rows(x, sign=-1)) < 1e-5
+
+
 def _smooth(n):
     for p in (2, 3, 5):
         while n % p == 0:
