@@ -268,8 +268,11 @@ hipError_t launch_ct_fused(const CtStep &step, const void *tw, const XposeDesc &
 
 // Rows alone that pass through LDS in the fused kernels go straight between
 // HBM and registers in a small array, where the way through LDS is latency
-// (64 points, 4 MB 0.81 of the time; 32 MB 0.73 to 1.9 times, by the length).
-constexpr int64_t kStraightBytes = 4 << 20;
+// (64 points, 4 MB 0.81 of the time; 32 MB 0.73 to 1.9 times, by the length);
+// rows of several whole lines up to 12 MB (through LDS / straight: 64 points,
+// 12 MB 6.3 / 4.6 us, complex128 40 points, 12 MB 7.3 / 5.5; but 48 points,
+// 16 MB 7.4 / 11.0, and rows of 256 bytes, 12 MB 1.0 to 1.9 times).
+constexpr int64_t kStraightBytes = 4 << 20, kStraightLineBytes = 12 << 20;
 
 // Rows that are not whole lines are copied as one block per group where the
 // array is too large for the Infinity Cache to join the lines' parts (729^3,
@@ -307,7 +310,8 @@ hipError_t launch_ct_rows(int N, bool fp64, const void *tw, int64_t nrows, int d
     if (grid >= (int64_t)0x7fffffff) return hipErrorInvalidValue;
     const int64_t row = (int64_t)N * e->esz, bytes = nrows * row;
     const bool block = e->rows_block && (bytes > kBlockBytes || (N % 2 != 0 && row < kBlockRowBytes));
-    const bool straight = e->rows_straight && bytes <= kStraightBytes;
+    const bool lines = row % 128 == 0 && row > 256;
+    const bool straight = e->rows_straight && bytes <= (lines ? kStraightLineBytes : kStraightBytes);
     // (parts of lines are left to the caches to join)
     const bool nt_store = policy.nt_store && (block || straight || row % 128 == 0 || 128 % row == 0);
     c.flags = (policy.nt_load ? kCtNtLoad : 0) | (nt_store ? kCtNtStore : 0) | (dir > 0 ? kCtInverse : 0) |
